@@ -168,6 +168,9 @@ __device__ __forceinline__ void store_hot(const BlockMem &m, void *state, int64_
 //     packed hand words (lane permutes) and compute the waits of the four hands side by side;
 //   - the owner lane writes the results into its state and takes the dealer's first draw.
 
+// readlane as an unsigned word: the builtin returns int, which would carry bit 31 into the upper half of a 64-bit value
+__device__ __forceinline__ uint32_t read_lane(uint32_t x, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)x, lane); }
+
 __device__ __forceinline__ void deal_wave(Ctx &c, bool need, void *state, int64_t B, int64_t b)
 {
   const int lane = threadIdx.x & 63;
@@ -179,10 +182,10 @@ __device__ __forceinline__ void deal_wave(Ctx &c, bool need, void *state, int64_
   while (pending) {
     const int src = __builtin_ctzll(pending);
     pending &= pending - 1;
-    const uint32_t serial = __builtin_amdgcn_readlane(my_serial, src);
-    const uint32_t env_id = __builtin_amdgcn_readlane(c.env_id, src);
-    const int dealer = (int)(__builtin_amdgcn_readlane(my_kyoku, src) & 3u);
-    const int64_t bsrc = (int64_t)(((uint64_t)__builtin_amdgcn_readlane(b_hi, src) << 32) | __builtin_amdgcn_readlane(b_lo, src));
+    const uint32_t serial = read_lane(my_serial, src);
+    const uint32_t env_id = read_lane(c.env_id, src);
+    const int dealer = (int)(read_lane(my_kyoku, src) & 3u);
+    const int64_t bsrc = (int64_t)(((uint64_t)read_lane(b_hi, src) << 32) | read_lane(b_lo, src));
     // swap targets: lane j holds k[4j .. 4j+3]; position 135 is never swapped (target = itself)
     uint32_t kv0 = 0, kv1 = 0, kv2 = 0, kv3 = 0;
     if (lane < 34) {
@@ -207,7 +210,7 @@ __device__ __forceinline__ void deal_wave(Ctx &c, bool need, void *state, int64_
       for (int t = 3; t >= 0; t--) {
         const uint32_t j = 4u * (uint32_t)jj + (uint32_t)t;
         if (j >= 135u) continue;
-        const uint32_t kj = __builtin_amdgcn_readlane(t == 0 ? kv0 : t == 1 ? kv1 : t == 2 ? kv2 : kv3, jj);
+        const uint32_t kj = read_lane(t == 0 ? kv0 : t == 1 ? kv1 : t == 2 ? kv2 : kv3, jj);
         q0 = (j < i0 && q0 == kj) ? j : q0;
         q1 = (j < i0 + 1u && q1 == kj) ? j : q1;
         q2 = (j < i0 + 2u && q2 == kj) ? j : q2;
@@ -217,7 +220,7 @@ __device__ __forceinline__ void deal_wave(Ctx &c, bool need, void *state, int64_
     // the wall: ids of positions 4*lane .. 4*lane+3 in the four bytes of lane's word
     const uint32_t wv = lane < 34 ? (q0 | q1 << 8 | q2 << 16 | q3 << 24) : 0u;
     // the wall goes to HBM, one word per lane
-    const int sel = (int)__builtin_amdgcn_readlane((uint32_t)c.g.wall_sel, src);
+    const int sel = (int)read_lane((uint32_t)c.g.wall_sel, src);
     if (lane < 34) (state_u32(state, B) + (int64_t)(kHotU32 + 11 + 34 * sel) * B + bsrc)[(int64_t)lane * B] = wv;
     // 4 x 13 tiles -> packed hand words: lane j < 4 collects the hand of seat wind j (its tiles come from the other
     // lanes' wall words by a lane permute; every lane takes part, lanes >= 4 repeat the work of lane & 3) and then
@@ -240,16 +243,16 @@ __device__ __forceinline__ void deal_wave(Ctx &c, bool need, void *state, int64_
     uint64_t wt = 0;
     if (lane < 4) wt = waits_of(&c.L, h0, h1, h2, h3, 0, 0);
     const uint32_t wt_lo = (uint32_t)wt, wt_hi = (uint32_t)(wt >> 32);
-    const uint32_t first_id = (__builtin_amdgcn_readlane(wv, 13) >> 0) & 255u;        // wall[52]
+    const uint32_t first_id = (read_lane(wv, 13) >> 0) & 255u;        // wall[52]
     if (lane == src) {
       deal_reset(c);
 #pragma unroll
       for (int j = 0; j < 4; j++) {
         const int s = (dealer + j) & 3;
-        HW(c, s, 0) = __builtin_amdgcn_readlane(h0, j); HW(c, s, 1) = __builtin_amdgcn_readlane(h1, j);
-        HW(c, s, 2) = __builtin_amdgcn_readlane(h2, j); HW(c, s, 3) = __builtin_amdgcn_readlane(h3, j);
-        SW(c, s) |= __builtin_amdgcn_readlane(reds, j);
-        WAITS(c, s) = (uint64_t)__builtin_amdgcn_readlane(wt_hi, j) << 32 | __builtin_amdgcn_readlane(wt_lo, j);
+        HW(c, s, 0) = read_lane(h0, j); HW(c, s, 1) = read_lane(h1, j);
+        HW(c, s, 2) = read_lane(h2, j); HW(c, s, 3) = read_lane(h3, j);
+        SW(c, s) |= read_lane(reds, j);
+        WAITS(c, s) = (uint64_t)read_lane(wt_hi, j) << 32 | read_lane(wt_lo, j);
       }
       // the dealer's first draw (wall[52]) without going through HBM
       c.g.draw_ptr = 53; c.g.live_left = 69; c.g.kanflags &= (uint8_t)~1u;

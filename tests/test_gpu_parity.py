@@ -286,6 +286,21 @@ def test_import_export_roundtrip():
     assert not d, d[:4]
 
 
+def test_deal_on_the_spot_of_a_hand_that_waits_on_kind_31():
+    """a deal that finds no hand made ahead (here: after an import) computes the waits across lanes; kind 31 is the top
+    bit of the lower half of the wait set"""
+    kw = dict(seed=5, flags=mjo.RULES_NORED, mode=mjo.MODE_HALF, env_id_base=253152)
+    o, g = mjo.Oracle(2, **kw), GpuEngine(2, **kw)
+    e = o.export()
+    e["kyoku_serial"], e["terminated"], e["phase"], e["mask"], e["actor_mask"] = 5, 1, 3, 0, 0
+    for x in (o, g):
+        x.import_(e)
+        x.reset_done()
+    assert int(o.export()["waits"][1].max()) >> 31 == 1          # the sixth deal of game 253153: a seat dealt tenpai
+    d = diff_records(o.export(), g.export())
+    assert not d, d[:4]
+
+
 def test_illegal_action():
     o, g = mjo.Oracle(8, 1), GpuEngine(8, seed=1)
     a = o.sample_random()
