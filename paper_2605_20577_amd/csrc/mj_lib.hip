@@ -1,6 +1,6 @@
 // libmj: HIP kernels (gfx950) and the C ABI of include/mj.h.
 //
-// Step kernels (k_rollout, k_step, k_new_games) map one lane to one environment, with LPW = 16 or 32 (or 64)
+// Step kernels (k_rollout, k_step, k_new_games) map one lane to one environment, with 1 to 32
 // environments per wavefront and the remaining lanes idle: the step is bound by instruction issue along divergent
 // paths, so narrower wavefronts and two of them per SIMD run faster than full ones.  A block of 128 lanes (two
 // wavefronts) stages into LDS the probe part of the per-suit pattern table (11 KB), the hot state arrays of its
@@ -54,27 +54,30 @@ constexpr int kRefillEvery = 64;         // steps between refills of the walls m
 constexpr int kStepRefillEvery = MJ_STEP_REFILL;   // the same for the one-step kernels
 static_assert(kRefillEvery % kHistFlushEvery == 0, "the history's staging ring is empty when the shuffle takes its column");
 
-// A step kernel may leave lanes of each wavefront idle: with LPW (lanes per wave) of 32 or 16 the same batch
-// occupies 2x or 4x as many wavefronts, which lets a SIMD overlap the LDS / memory latency of one wavefront
-// with the instructions of another and shrinks the set of divergent paths per wavefront.  The step is bound by
-// dependent-access latency, not by lane count, so small batches run faster that way.
+// A step kernel leaves lanes of each wavefront idle.  What bounds it is the chain of dependent instructions of a
+// wavefront, which grows with the number of games it carries (the union of their paths): one game per wavefront needs
+// 932 vector + 339 scalar instructions and 5.4 us per step, 32 games 1,691 + 624 and 9.4 us, while two wavefronts on a
+// SIMD take hardly longer than one.  So a batch is spread over all wavefront slots of the machine (pick_lanes).
 // LDS of a step kernel: probe tables | hot u64 arrays | hot u32 arrays | 136 wall bytes per env | one byte per env
 // (between two shuffles the wall bytes of an environment stage its action history, see hist_push; the last byte
 // says where the staged entries start)
-__host__ __device__ inline int envs_per_block(int lpw) { return (kBlock / 64) * lpw; }
-__host__ __device__ inline size_t step_lds_bytes(int probe_bytes, int lpw)
+constexpr int kMaxLanes = 32;            // environments a wavefront carries at most
+constexpr int kSlots = (kBlock / 64) * kMaxLanes;      // environment slots of a block = stride of its LDS arrays
+__host__ __device__ inline int envs_per_block(int lanes) { return (kBlock / 64) * lanes; }
+__host__ __device__ inline size_t step_lds_bytes(int probe_bytes)
 {
-  return (size_t)probe_bytes + (size_t)envs_per_block(lpw) * (kHotBytesPerEnv + 136 + 1);
+  return (size_t)probe_bytes + (size_t)kSlots * (kHotBytesPerEnv + 136 + 1);
 }
 
 struct BlockMem {
   Lut L;                                 // table pointers: the probe tables in LDS, the records in HBM.  Held by value
                                          // (in registers) so that the probes compile to LDS reads, not flat loads.
-  uint64_t *hq;                          // [kHotU64][envs per block]
-  uint32_t *hw;                          // [kHotU32][envs per block]
-  uint8_t *col;                          // this lane's column of the [136][envs per block] shuffle area
-  uint8_t *hbase;                        // this lane's byte of the [envs per block] area behind the shuffle area
-  int epb, idx;                          // envs per block; this lane's env slot in the block
+  uint64_t *hq;                          // [kHotU64][kSlots]
+  uint32_t *hw;                          // [kHotU32][kSlots]
+  uint8_t *col;                          // this lane's column of the [136][kSlots] shuffle area
+  uint8_t *hbase;                        // this lane's byte of the [kSlots] area behind the shuffle area
+  int idx;                               // this lane's slot in the block
+  int64_t b;                             // the environment it carries, counted from the launch's first one
   bool lane_on;                          // this lane carries an environment
 };
 
@@ -105,28 +108,27 @@ __device__ __forceinline__ void table_commit(const DevTables &T, uint8_t *lds, c
     if (i < n) dst[i] = r.v[k];
   }
 }
-// carve up the block's LDS (no memory traffic)
-template <int LPW>
-__device__ __forceinline__ BlockMem carve_block(const DevTables &T, uint8_t *lds)
+// carve up the block's LDS (no memory traffic); `lanes` = environments per wavefront of this launch
+__device__ __forceinline__ BlockMem carve_block(const DevTables &T, uint8_t *lds, int lanes)
 {
   BlockMem m;
-  m.epb = envs_per_block(LPW);
-  m.idx = (int)(threadIdx.x >> 6) * LPW + (int)(threadIdx.x & 63);
-  m.lane_on = (threadIdx.x & 63) < LPW;
+  const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+  m.lane_on = lane < lanes;
+  m.idx = wave * kMaxLanes + (lane & (kMaxLanes - 1));
+  m.b = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * lanes + lane;
   m.hq = (uint64_t *)(lds + T.probe_bytes);
-  m.hw = (uint32_t *)(lds + T.probe_bytes + (size_t)m.epb * 8 * kHotU64);
+  m.hw = (uint32_t *)(lds + T.probe_bytes + (size_t)kSlots * 8 * kHotU64);
   m.L.rowid = lds;
   m.L.bitmap = (const uint32_t *)(lds + kRowIdBytes);
   m.L.base = T.base; m.L.rowrank = T.rowrank; m.L.recs = T.recs; m.L.nb = T.nb;
-  m.col = lds + T.probe_bytes + (size_t)m.epb * kHotBytesPerEnv + m.idx;
-  m.hbase = lds + T.probe_bytes + (size_t)m.epb * (kHotBytesPerEnv + 136) + m.idx;
+  m.col = lds + T.probe_bytes + (size_t)kSlots * kHotBytesPerEnv + m.idx;
+  m.hbase = lds + T.probe_bytes + (size_t)kSlots * (kHotBytesPerEnv + 136) + m.idx;
   return m;
 }
 // ... and copy the probe tables in (ends with a block barrier)
-template <int LPW>
-__device__ __forceinline__ BlockMem stage_block(const DevTables &T, uint8_t *lds)
+__device__ __forceinline__ BlockMem stage_block(const DevTables &T, uint8_t *lds, int lanes)
 {
-  BlockMem m = carve_block<LPW>(T, lds);
+  BlockMem m = carve_block(T, lds, lanes);
   const TableRegs r = table_fetch(T);
   table_commit(T, lds, r);
   __syncthreads();
@@ -136,7 +138,7 @@ __device__ __forceinline__ BlockMem stage_block(const DevTables &T, uint8_t *lds
 __device__ __forceinline__ Env block_env(const BlockMem &m, void *state, int64_t B, int64_t b)
 {
   Env e = make_env(state, B, b);
-  set_hot(e, m.hq + m.idx, m.hw + m.idx, m.epb);
+  set_hot(e, m.hq + m.idx, m.hw + m.idx, kSlots);
   return e;
 }
 __device__ __forceinline__ void load_hot(const BlockMem &m, void *state, int64_t B, int64_t b)
@@ -144,18 +146,18 @@ __device__ __forceinline__ void load_hot(const BlockMem &m, void *state, int64_t
   const uint64_t *gq = state_u64(state, B) + b;
   const uint32_t *gw = state_u32(state, B) + b;
 #pragma unroll
-  for (int f = 0; f < kHotU64; f++) m.hq[f * m.epb + m.idx] = gq[(int64_t)f * B];
+  for (int f = 0; f < kHotU64; f++) m.hq[f * kSlots + m.idx] = gq[(int64_t)f * B];
 #pragma unroll
-  for (int f = 0; f < kHotU32; f++) m.hw[f * m.epb + m.idx] = gw[(int64_t)f * B];
+  for (int f = 0; f < kHotU32; f++) m.hw[f * kSlots + m.idx] = gw[(int64_t)f * B];
 }
 __device__ __forceinline__ void store_hot(const BlockMem &m, void *state, int64_t B, int64_t b)
 {
   uint64_t *gq = state_u64(state, B) + b;
   uint32_t *gw = state_u32(state, B) + b;
 #pragma unroll
-  for (int f = 0; f < kHotU64; f++) gq[(int64_t)f * B] = m.hq[f * m.epb + m.idx];
+  for (int f = 0; f < kHotU64; f++) gq[(int64_t)f * B] = m.hq[f * kSlots + m.idx];
 #pragma unroll
-  for (int f = 0; f < kHotU32; f++) gw[(int64_t)f * B] = m.hw[f * m.epb + m.idx];
+  for (int f = 0; f < kHotU32; f++) gw[(int64_t)f * B] = m.hw[f * kSlots + m.idx];
 }
 
 // Deal for every lane of the wavefront that needs one.  All 64 lanes must call this together.
@@ -370,20 +372,17 @@ __device__ __forceinline__ void reset_env(Ctx &c, bool first)
 
 // mode 0: first initialisation of every env; mode 1: restart of the terminated ones (a block without a
 // terminated env leaves before it stages anything)
-template <int LPW>
-__global__ void __launch_bounds__(kBlock, MJ_OCC) k_new_games(void *state, int64_t B, Rules R, DevTables T, int mode)
+__global__ void __launch_bounds__(kBlock, MJ_OCC) k_new_games(void *state, int64_t B, Rules R, DevTables T, int lanes, int mode)
 {
   extern __shared__ __align__(16) uint8_t lds[];
+  BlockMem m = carve_block(T, lds, lanes);
+  const int64_t b = m.b;
+  const bool active = m.lane_on && b < B;
   if (mode == 1) {
-    const int idx = (int)(threadIdx.x >> 6) * LPW + (int)(threadIdx.x & 63);
-    const int64_t b0 = (int64_t)blockIdx.x * envs_per_block(LPW) + idx;
     int term = 0;
-    if ((threadIdx.x & 63) < LPW && b0 < B) term = (int)(make_env(state, B, b0).glob[0] >> 24 & 0xFFu);   // Glob::terminated
+    if (active) term = (int)(make_env(state, B, b).glob[0] >> 24 & 0xFFu);   // Glob::terminated
     if (!__syncthreads_or(term)) return;
   }
-  BlockMem m = carve_block<LPW>(T, lds);
-  const int64_t b = (int64_t)blockIdx.x * m.epb + m.idx;
-  const bool active = m.lane_on && b < B;
   Ctx c;
   c.e = block_env(m, state, B, active ? b : 0); c.L = m.L; c.R = R; c.env_id = R.env_id_base + (uint32_t)b;
   c.need_deal = false; c.need_turn = false; c.live_ptr = -1;
@@ -395,12 +394,12 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_new_games(void *state, int64
   if (active) {
     if (mode == 0) {
       reset_env(c, true); touched = true;
-      refill_next_wall(c, m.col, m.epb, 0);          // every lane deals now: make the first walls side by side
+      refill_next_wall(c, m.col, kSlots, 0);          // every lane deals now: make the first walls side by side
     } else if (c.g.terminated) { reset_env(c, false); touched = true; }
   }
   deal_stage(c, active, state, B, b);
   if (touched) { step_finish(c); store_hot(m, state, B, b); store_glob(c.e, c.g); }
-  if (mode == 0 && active) refill_next_wall(c, m.col, m.epb, 1);
+  if (mode == 0 && active) refill_next_wall(c, m.col, kSlots, 1);
 }
 
 #ifdef MJ_PROFILE
@@ -415,8 +414,7 @@ struct StepOut {
   uint8_t *terminated;     // [B] the game ended with this step (or had ended before)
 };
 
-template <int LPW>
-__global__ void __launch_bounds__(kBlock, MJ_OCC) k_step(void *state, int64_t B, Rules R, DevTables T, const int8_t *actions, int refill,
+__global__ void __launch_bounds__(kBlock, MJ_OCC) k_step(void *state, int64_t B, Rules R, DevTables T, int lanes, const int8_t *actions, int refill,
                                                  int auto_reset, StepOut out)
 {
   extern __shared__ __align__(16) uint8_t lds[];
@@ -429,8 +427,8 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_step(void *state, int64_t B,
 #else
 #define MJ_PT(i) ((void)0)
 #endif
-  BlockMem m = carve_block<LPW>(T, lds);
-  const int64_t b = (int64_t)blockIdx.x * m.epb + m.idx;
+  BlockMem m = carve_block(T, lds, lanes);
+  const int64_t b = m.b;
   const bool active = m.lane_on && b < B;
   Ctx c;
   c.e = block_env(m, state, B, active ? b : 0); c.L = m.L; c.R = R; c.env_id = R.env_id_base + (uint32_t)b;
@@ -447,7 +445,7 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_step(void *state, int64_t B,
   __syncthreads();
   MJ_PT(1);
   if (active) {
-    if (refill && c.e.nserial[0] != c.e.serial[0] + 1) refill_next_wall(c, m.col, m.epb, c.e.serial[0] + 1);
+    if (refill && c.e.nserial[0] != c.e.serial[0] + 1) refill_next_wall(c, m.col, kSlots, c.e.serial[0] + 1);
     MJ_PT(2);
     step_env(c, acts);
     MJ_PT(3);
@@ -512,13 +510,12 @@ __device__ __forceinline__ uint32_t sample_actors(Ctx &c, uint64_t step, int &ro
 }
 
 // n_steps of { sample, step, optional reset } without leaving the kernel: environments never interact
-template <int LPW>
-__global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t B, Rules R, DevTables T, uint64_t step0,
+__global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t B, Rules R, DevTables T, int lanes, uint64_t step0,
                                                     int n_steps, int auto_reset, int64_t env_lo, int64_t env_hi)
 {
   extern __shared__ __align__(16) uint8_t lds[];
-  BlockMem m = carve_block<LPW>(T, lds);
-  const int64_t b = env_lo + (int64_t)blockIdx.x * m.epb + m.idx;      // the launch covers environments [env_lo, env_hi)
+  BlockMem m = carve_block(T, lds, lanes);
+  const int64_t b = env_lo + m.b;      // the launch covers environments [env_lo, env_hi)
   const bool active = m.lane_on && b < env_hi;
   Ctx c;
   c.e = block_env(m, state, B, active ? b : 0); c.L = m.L; c.R = R; c.env_id = R.env_id_base + (uint32_t)b;
@@ -546,7 +543,7 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t
       if ((step0 + t) % kHistFlushEvery == 0) {
         hist_flush(c.e, c.g.hist_len);                 // the shuffle needs the column that stages the history
         if ((step0 + t) % kRefillEvery == 0 && c.e.nserial[0] != c.e.serial[0] + 1)
-          refill_next_wall(c, m.col, m.epb, c.e.serial[0] + 1);
+          refill_next_wall(c, m.col, kSlots, c.e.serial[0] + 1);
       }
       MJ_RE(rf, PR_REFILL);
       int ron_offered;
@@ -594,7 +591,7 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_deal_from_wall(void *state, 
                                                            const uint8_t *wall)
 {
   extern __shared__ __align__(16) uint8_t lds[];
-  BlockMem m = stage_block<64>(T, lds);
+  BlockMem m = stage_block(T, lds, 1);
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   Ctx c;
   c.e = make_env(state, B, b); c.L = m.L; c.R = R; c.env_id = R.env_id_base + (uint32_t)b;
@@ -1009,7 +1006,7 @@ struct MjHandle {
   unsigned *obs_ctr;                     // work counters of the observation writer (device, zero between launches)
   int n_cu;
   size_t lds_bytes, probe_bytes;
-  int lpw;
+  int lanes;                             // environments per wavefront of the step kernels
   hipEvent_t ev[2];
   int ev_steps;
   bool ev_valid;
@@ -1057,25 +1054,25 @@ ScratchLayout scratch_layout()
 }
 size_t scratch_bytes_impl() { return scratch_layout().total; }
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kAuxBlock - 1) / kAuxBlock); }
-inline unsigned step_blocks(int64_t n, int lpw) { int e = envs_per_block(lpw); return (unsigned)((n + e - 1) / e); }
-// lanes per wave for a batch: fill the machine's wave slots (256 CUs x 4 SIMDs x 2 resident waves of this kernel)
-inline int pick_lpw(int64_t B)
+inline unsigned step_blocks(int64_t n, int lanes) { int e = envs_per_block(lanes); return (unsigned)((n + e - 1) / e); }
+// Environments per wavefront for a batch: as few as fill every wavefront slot once (8 per compute unit: two per SIMD is
+// what the registers of these kernels allow), at most 32.  Measured, us per step inside 512-step launches, 16 per
+// wavefront as against this rule (red rules): 256 games 9.6 -> 5.9 (1 each), 2,048: 10.0 -> 5.4 (1), 4,096: 9.9 -> 6.6
+// (2), 8,192: 9.6 -> 7.5 (4), 16,384: 9.0 -> 8.4 (8), 49,152: 17.1 -> 9.0 (24).  More than one round of wavefronts
+// doubles the time (4,096 games, 1 each: 14.5), fewer wavefronts with more games lose at every size (2,048 games, 2
+// each: 8.6).  64 per wavefront leave LDS for one wavefront per SIMD and lost at every size up to 2^20.
+// MJ_LPW overrides the number for experiments.
+inline int pick_lanes(int64_t B, int n_cu)
 {
   const char *ov = std::getenv("MJ_LPW");
-  if (ov) { int v = std::atoi(ov); if (v == 64 || v == 32 || v == 16) return v; }
-  if (B >= 2048 * 32) return 32;        // also for larger batches: 64 per wavefront leaves room for one wavefront
-                                        // per SIMD only (LDS), measured slower at every batch size
-  return 16;
+  if (ov) { int v = std::atoi(ov); if (v >= 1) return v < kMaxLanes ? v : kMaxLanes; }
+  const int64_t slots = (int64_t)n_cu * 8;
+  const int64_t lanes = (B + slots - 1) / slots;
+  return (int)(lanes < kMaxLanes ? lanes : kMaxLanes);
 }
-#define MJ_LAUNCH_STEP(kern, h, st, ...) MJ_LAUNCH_STEP_N(kern, h, st, (h)->B, __VA_ARGS__)
-#define MJ_LAUNCH_STEP_N(kern, h, st, n_envs, ...)                                                               \
-  do {                                                                                                           \
-    size_t lds_ = step_lds_bytes((int)(h)->probe_bytes, (h)->lpw);                                               \
-    unsigned nb_ = step_blocks((n_envs), (h)->lpw);                                                              \
-    if ((h)->lpw == 64) kern<64><<<nb_, kBlock, lds_, st>>>(__VA_ARGS__);                                        \
-    else if ((h)->lpw == 32) kern<32><<<nb_, kBlock, lds_, st>>>(__VA_ARGS__);                                   \
-    else kern<16><<<nb_, kBlock, lds_, st>>>(__VA_ARGS__);                                                       \
-  } while (0)
+// a step kernel over n_envs environments: its arguments start with (state, B, rules, tables, environments per wavefront)
+#define MJ_LAUNCH_STEP(kern, h, st, n_envs, ...)                                                                 \
+  kern<<<step_blocks((n_envs), (h)->lanes), kBlock, (h)->lds_bytes, st>>>((h)->d_state, (h)->B, (h)->R, (h)->T, (h)->lanes, __VA_ARGS__)
 inline int check(hipError_t e) { return e == hipSuccess ? MJ_OK : MJ_E_HIP; }
 
 // ---- tables for callers that can not allocate (mj_eval_hands_static) ----------------------------------------
@@ -1171,8 +1168,8 @@ int mj_init(MjHandle **out, void *d_state, void *d_scratch, int64_t B, uint64_t 
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
       hipDeviceGetAttribute(&h->n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || h->n_cu <= 0) { delete h; return MJ_E_HIP; }
-  h->lpw = pick_lpw(B);
-  h->lds_bytes = step_lds_bytes((int)sl.probe_bytes, 64);
+  h->lanes = pick_lanes(B, h->n_cu);
+  h->lds_bytes = step_lds_bytes((int)sl.probe_bytes);
   h->probe_bytes = sl.probe_bytes;
   if ((size_t)lds_max < h->lds_bytes) { delete h; return MJ_E_UNSUPPORTED; }
   hipStream_t st = (hipStream_t)stream;
@@ -1202,7 +1199,7 @@ int mj_init(MjHandle **out, void *d_state, void *d_scratch, int64_t B, uint64_t 
   if (rc == MJ_OK) rc = check(hipEventCreate(&h->ev[0]));
   if (rc == MJ_OK) rc = check(hipEventCreate(&h->ev[1]));
   if (rc != MJ_OK) { delete h; return rc; }
-  MJ_LAUNCH_STEP(k_new_games, h, st, d_state, B, h->R, h->T, 0);
+  MJ_LAUNCH_STEP(k_new_games, h, st, B, 0);
   rc = check(hipGetLastError());
   if (rc != MJ_OK) { delete h; return rc; }
   *out = h;
@@ -1212,7 +1209,7 @@ int mj_init(MjHandle **out, void *d_state, void *d_scratch, int64_t B, uint64_t 
 int mj_step(MjHandle *h, const int8_t *d_actions, void *stream)
 {
   if (!h || !d_actions || ((uintptr_t)d_actions & 3)) return MJ_E_ARG;
-  MJ_LAUNCH_STEP(k_step, h, (hipStream_t)stream, h->d_state, h->B, h->R, h->T, d_actions, (int)(h->step % kStepRefillEvery == 0), 0,
+  MJ_LAUNCH_STEP(k_step, h, (hipStream_t)stream, h->B, d_actions, (int)(h->step % kStepRefillEvery == 0), 0,
                  StepOut{nullptr, nullptr, nullptr, nullptr});
   h->step++;
   return check(hipGetLastError());
@@ -1224,7 +1221,7 @@ int mj_step_full(MjHandle *h, const int8_t *d_actions, int auto_reset, uint64_t 
   if (!h || !d_actions || ((uintptr_t)d_actions & 3) || ((uintptr_t)d_mask & 15) || ((uintptr_t)d_delta & 15) ||
       ((uintptr_t)d_reward & 15))
     return MJ_E_ARG;
-  MJ_LAUNCH_STEP(k_step, h, (hipStream_t)stream, h->d_state, h->B, h->R, h->T, d_actions, (int)(h->step % kStepRefillEvery == 0),
+  MJ_LAUNCH_STEP(k_step, h, (hipStream_t)stream, h->B, d_actions, (int)(h->step % kStepRefillEvery == 0),
                  auto_reset ? 1 : 0, StepOut{d_mask, d_delta, d_reward, d_terminated});
   h->step++;
   return check(hipGetLastError());
@@ -1277,7 +1274,7 @@ int mj_standings(const MjHandle *h, int32_t *d_score, uint8_t *d_rank, void *str
 int mj_reset_done(MjHandle *h, void *stream)
 {
   if (!h) return MJ_E_ARG;
-  MJ_LAUNCH_STEP(k_new_games, h, (hipStream_t)stream, h->d_state, h->B, h->R, h->T, 1);
+  MJ_LAUNCH_STEP(k_new_games, h, (hipStream_t)stream, h->B, 1);
   return check(hipGetLastError());
 }
 
@@ -1310,21 +1307,21 @@ int mj_step_random(MjHandle *h, int32_t n_steps, int auto_reset, int write_obs, 
     // over x slices' worth of games takes about x + 0.5 (x = 2 / 3 / 4: 2.6 / 3.5 / 4.3; B = 131,072: 5.3 G env
     // steps/s) and only from x = 6 on about x; sliced launches take ceil(x), however small the last slice is
     // (B = 131,072: 7.0 G).  So slices are used when the last one is more than half full.
-    const int64_t resident = (int64_t)h->n_cu * 4 * envs_per_block(h->lpw);
+    const int64_t resident = (int64_t)h->n_cu * 4 * envs_per_block(h->lanes);
     const int64_t tail = h->B % resident;
-    const bool slices = h->lpw == 32 && h->B <= 6 * resident && (tail == 0 || 2 * tail > resident);
+    const bool slices = h->lanes == kMaxLanes && h->B <= 6 * resident && (tail == 0 || 2 * tail > resident);
     const int64_t per_slice = slices ? resident : h->B;
     for (int t = 0; t < n_steps && rc == MJ_OK; t += chunk) {
       int n = n_steps - t < chunk ? n_steps - t : chunk;
       for (int64_t lo = 0; lo < h->B && rc == MJ_OK; lo += per_slice) {
         const int64_t hi = lo + per_slice < h->B ? lo + per_slice : h->B;
-        MJ_LAUNCH_STEP_N(k_rollout, h, st, hi - lo, h->d_state, h->B, h->R, h->T, h->step + t, n, auto_reset, lo, hi);
+        MJ_LAUNCH_STEP(k_rollout, h, st, hi - lo, h->step + t, n, auto_reset, lo, hi);
         rc = check(hipGetLastError());
       }
     }
   } else {
     for (int t = 0; t < n_steps && rc == MJ_OK; t++) {
-      MJ_LAUNCH_STEP(k_rollout, h, st, h->d_state, h->B, h->R, h->T, h->step + t, 1, auto_reset, (int64_t)0, h->B);
+      MJ_LAUNCH_STEP(k_rollout, h, st, h->B, h->step + t, 1, auto_reset, (int64_t)0, h->B);
       rc = check(hipGetLastError());
       if (rc == MJ_OK) rc = mj_observe(h, d_obs, stream);
     }

@@ -162,6 +162,24 @@ def test_every_lanes_per_wave_variant(lpw, monkeypatch):
     assert not diff_records(o.export(), g.export())
 
 
+@pytest.mark.parametrize("B,lanes", [(1, 1), (77, 1), (77, 3), (130, 31), (2047, 0), (2049, 0), (4097, 0)])
+def test_games_per_wavefront(B, lanes, monkeypatch):
+    """any number of games per wavefront, forced (last wavefront and block partly filled) or picked by the batch size (0);
+    fused steps, steps one at a time, restarts"""
+    if lanes:
+        monkeypatch.setenv("MJ_LPW", str(lanes))
+    kw = dict(seed=33, flags=mjo.RULES_RED, mode=mjo.MODE_SINGLE)
+    o, g = mjo.Oracle(B, **kw), GpuEngine(B, **kw)
+    o.step_random(150); g.step_random(150)
+    assert not diff_records(o.export(), g.export())
+    for _ in range(5):
+        a = o.sample_random()
+        assert np.array_equal(a, g.sample_random())
+        o.step(a); g.step(a)
+        o.reset_done(); g.reset_done()
+    assert not diff_records(o.export(), g.export())
+
+
 def test_full_size_sampled_envs():
     """B=65,536 in the benchmark's launch shape; sampled environments recomputed one by one by the oracle"""
     B, steps = 65536, 400
