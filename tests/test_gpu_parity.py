@@ -304,6 +304,33 @@ def test_import_export_roundtrip():
     assert not d, d[:4]
 
 
+@pytest.mark.parametrize("lo,n", [(0, 1), (7, 63), (1, 64), (66, 65), (0, 131)])
+def test_export_import_ranges(lo, n):
+    """records of any range of an odd batch (full and ragged groups of 64), out and back in at the same place, with every rule
+    flag that uses a record field; arbitrary bytes in the fields that an import masks or clamps"""
+    kw = dict(seed=19, flags=mjo.RULES_RED | mjo.F_KANDORA_LATE, mode=mjo.MODE_HALF)
+    o, g = mjo.Oracle(131, **kw), GpuEngine(131, **kw)
+    o.step_random(700); g.step_random(700)
+    e = o.export()
+    assert not diff_records(e[lo:lo + n], g.export(lo, n))
+    other = mjo.Oracle(131, **dict(kw, seed=20))
+    other.step_random(650)
+    f = other.export()
+    g.import_(f[lo:lo + n], lo)
+    want = e.copy()
+    want[lo:lo + n] = f[lo:lo + n]
+    assert not diff_records(want, g.export())
+    raw = f[lo:lo + n].copy()
+    for name in ("ippatsu", "first_turn", "furiten_temp", "furiten_riichi", "rinshan", "dora_pending"):
+        raw[name] |= 0xFE
+    raw["n_hist"] = 200
+    g.import_(raw, lo)
+    got = g.export(lo, n)
+    assert np.array_equal(got["n_hist"], np.full(n, 128)) and np.array_equal(got["hist"], raw["hist"])
+    for name in ("ippatsu", "first_turn", "furiten_temp", "furiten_riichi", "rinshan", "dora_pending"):
+        assert np.array_equal(got[name], f[name][lo:lo + n]), name
+
+
 def test_deal_on_the_spot_of_a_hand_that_waits_on_kind_31():
     """a deal that finds no hand made ahead (here: after an import) computes the waits across lanes; kind 31 is the top
     bit of the lower half of the wait set"""
