@@ -839,15 +839,19 @@ MJ_HD void eval_placed(EvalCtx &c, const Decomp &d, uint64_t trip_c, uint64_t tr
   offer(c, y, ym, fu);
 }
 
-// all ways the winning tile can sit in this decomposition
+// All ways the winning tile can sit in this decomposition: the pair or the middle or edge of a run (both leave the sets as
+// they are and are worth 2 fu: one way), a triplet, the open end of a run.
+// MANY: whole wavefronts evaluate hands.  The ways are then walked in a loop around ONE copy of eval_placed, which the
+// wavefront runs as often as its busiest lane needs (mostly once or twice), not once per kind of way that any of its
+// lanes has: 2^20 hands 58.0 -> 44.5 us.  In a step a win is evaluated by a lane or two, for which straight code is the
+// shorter chain (65,536 games: 8.44 us per step, 8.53 with the loop).
+template <bool MANY>
 MJ_HD void eval_decomp(EvalCtx &c, const Decomp &d)
 {
-  int w = c.win;
-  if (d.pair == w) eval_placed(c, d, d.trip_c, d.trip_o, 2, false);
-  if (d.trip_c & kbit(w)) {
-    if (c.tsumo) eval_placed(c, d, d.trip_c, d.trip_o, 0, false);
-    else eval_placed(c, d, d.trip_c & ~kbit(w), d.trip_o | kbit(w), 0, false);
-  }
+  enum : uint32_t { CLOSED = 1, TRIPLET = 2, OPEN_END = 4 };
+  const int w = c.win;
+  uint32_t ways = d.pair == w ? CLOSED : 0u;
+  if (d.trip_c & kbit(w)) ways |= TRIPLET;
   if (w < 27) {
     int su = suit_of(w), r = rank_of(w, su);
     uint32_t cr = pick4(d.crun[0], d.crun[1], d.crun[2], 0u, su);
@@ -856,11 +860,26 @@ MJ_HD void eval_decomp(EvalCtx &c, const Decomp &d)
     bool high = r >= 2 && cnt3(cr, r - 2) > 0;                          // run r-2, r-1, r
     bool edge = (low && r == 6) || (high && r == 2);
     bool two = (low && r != 6) || (high && r != 2);
-    if (mid || edge) eval_placed(c, d, d.trip_c, d.trip_o, 2, false);
-    if (two) eval_placed(c, d, d.trip_c, d.trip_o, 0, true);
+    if (mid || edge) ways |= CLOSED;
+    if (two) ways |= OPEN_END;
+  }
+  const uint64_t called = c.tsumo ? 0ull : kbit(w);      // a triplet completed by another seat's tile counts as called
+  if (MANY) {
+#pragma unroll 1
+    while (ways) {
+      const uint32_t way = ways & (0u - ways);
+      ways ^= way;
+      const uint64_t moved = way == TRIPLET ? called : 0ull;
+      eval_placed(c, d, d.trip_c & ~moved, d.trip_o | moved, way == CLOSED ? 2 : 0, way == OPEN_END);
+    }
+  } else {
+    if (ways & CLOSED) eval_placed(c, d, d.trip_c, d.trip_o, 2, false);
+    if (ways & TRIPLET) eval_placed(c, d, d.trip_c & ~called, d.trip_o | called, 0, false);
+    if (ways & OPEN_END) eval_placed(c, d, d.trip_c, d.trip_o, 0, true);
   }
 }
 
+template <bool MANY = false>
 MJ_HD void eval_hand(const Lut *Lp, const HandIn &q, HandOut &out)
 {
   const Lut &L = *Lp;
@@ -935,9 +954,13 @@ MJ_HD void eval_hand(const Lut *Lp, const HandIn &q, HandOut &out)
   }
   c.riichi = c.menzen ? q.riichi : 0;
   c.n_dora = c.n_ura = 0;
+  // the indicators as two words, one byte each: an array indexed in a loop would be scratch memory
+  uint64_t ind = 0, ura = 0;
+#pragma unroll
+  for (int i = 0; i < 5; i++) { ind |= (uint64_t)q.ind[i] << (8 * i); ura |= (uint64_t)q.ura[i] << (8 * i); }
   for (int i = 0; i < q.n_ind && i < 5; i++) {
-    c.n_dora += hand_count(all, dora_of(q.ind[i]));
-    if (c.riichi) c.n_ura += hand_count(all, dora_of(q.ura[i]));
+    c.n_dora += hand_count(all, dora_of((int)(ind >> (8 * i) & 255u)));
+    if (c.riichi) c.n_ura += hand_count(all, dora_of((int)(ura >> (8 * i) & 255u)));
   }
   c.n_aka = q.n_aka;
   int f = q.flags;
@@ -992,7 +1015,7 @@ MJ_HD void eval_hand(const Lut *Lp, const HandIn &q, HandOut &out)
           add_record(d, i0 == 0 ? rec0[0] : L.recs[4 * (size_t)key[0] + i0], 0);
           add_record(d, i1 == 0 ? rec0[1] : L.recs[4 * (size_t)key[1] + i1], 1);
           add_record(d, i2 == 0 ? rec0[2] : L.recs[4 * (size_t)key[2] + i2], 2);
-          eval_decomp(c, d);
+          eval_decomp<MANY>(c, d);
         }
     c.colour_ym &= ~gates;
   }

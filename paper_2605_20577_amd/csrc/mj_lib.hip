@@ -85,6 +85,7 @@ struct BlockMem {
 // between them: table_fetch starts the loads (all in flight together), table_commit writes them to LDS.  A caller
 // that loads its hot state in between pays one memory round trip for both.
 constexpr int kTableChunks = 6;          // 16-byte chunks per lane: 6 x 128 lanes x 16 B = 12 KB >= the probe tables
+constexpr int kEvalChunks = (kTableChunks * kBlock + kAuxBlock - 1) / kAuxBlock;     // the same for blocks of kAuxBlock lanes
 struct TableRegs { uint4 v[kTableChunks]; };
 __device__ __forceinline__ TableRegs table_fetch(const DevTables &T)
 {
@@ -845,46 +846,65 @@ __global__ void __launch_bounds__(kRecBlock) k_import(void *state, int64_t B, in
   }
 }
 
-__global__ void __launch_bounds__(kAuxBlock, MJ_OCC) k_eval_hands(DevTables T, int64_t n, const MjHandQuery *in, MjHandResult *out)
+// Hand evaluator: one lane per hand, `lanes` hands per wavefront (eval_lanes).
+__global__ void __launch_bounds__(kAuxBlock, MJ_OCC) k_eval_hands(DevTables T, int lanes, int64_t n, const MjHandQuery *in, MjHandResult *out)
 {
   extern __shared__ __align__(16) uint8_t lds[];
+  const int lane = (int)(threadIdx.x & 63);
+  const int64_t i = ((int64_t)blockIdx.x * (kAuxBlock / 64) + (threadIdx.x >> 6)) * lanes + lane;
+  const bool on = lane < lanes && i < n;
+  // the query's sixteen words travel with the tables: one memory round trip
+  uint32_t w[16];
+  const uint4 *qw = (const uint4 *)(in + (on ? i : 0));
+#pragma unroll
+  for (int j = 0; j < 4; j++) {
+    const uint4 v = qw[j];
+    w[4 * j] = v.x; w[4 * j + 1] = v.y; w[4 * j + 2] = v.z; w[4 * j + 3] = v.w;
+  }
   {
     const uint4 *src = (const uint4 *)T.probe;
     uint4 *dst = (uint4 *)lds;
-    for (int j = threadIdx.x; j < T.probe_bytes / 16; j += blockDim.x) dst[j] = src[j];
+    const int chunks = T.probe_bytes / 16;
+    uint4 v[kEvalChunks];
+#pragma unroll
+    for (int k = 0; k < kEvalChunks; k++) { const int j = (int)threadIdx.x + k * kAuxBlock; v[k] = j < chunks ? src[j] : make_uint4(0, 0, 0, 0); }
+#pragma unroll
+    for (int k = 0; k < kEvalChunks; k++) { const int j = (int)threadIdx.x + k * kAuxBlock; if (j < chunks) dst[j] = v[k]; }
     __syncthreads();
   }
-  Lut Lv;
-  Lv.rowid = lds; Lv.bitmap = (const uint32_t *)(lds + kRowIdBytes);
-  Lv.base = T.base; Lv.rowrank = T.rowrank; Lv.recs = T.recs; Lv.nb = T.nb;
-  const Lut *L = &Lv;
-  int64_t i = (int64_t)blockIdx.x * kAuxBlock + threadIdx.x;
-  if (i >= n) return;
-  const uint32_t *qw = (const uint32_t *)(in + i);
-  uint32_t w[16];
-#pragma unroll
-  for (int j = 0; j < 4; j++) {
-    uint4 v = ((const uint4 *)qw)[j];
-    w[4 * j] = v.x; w[4 * j + 1] = v.y; w[4 * j + 2] = v.z; w[4 * j + 3] = v.w;
-  }
-  MjHandQuery q;
-  __builtin_memcpy(&q, w, 64);
+  if (!on) return;
+  Lut L;
+  L.rowid = lds; L.bitmap = (const uint32_t *)(lds + kRowIdBytes);
+  L.base = T.base; L.rowrank = T.rowrank; L.recs = T.recs; L.nb = T.nb;
+  // byte `at` of the record; `at` is a constant everywhere, so the record stays in registers
+  auto byte_of = [&](size_t at) { return w[at >> 2] >> (8 * (at & 3)) & 255u; };
+  auto half_of = [&](size_t at) { return w[at >> 2] >> (8 * (at & 3)) & 0xFFFFu; };
   HandIn hi;
+#pragma unroll
   for (int su = 0; su < 4; su++) {
     uint32_t hw = 0;
-    int nr = su == 3 ? 7 : 9;
-    for (int r = 0; r < nr; r++) {
-      uint32_t cnt = q.hand[(su == 3 ? 27 : 9 * su) + r];
+#pragma unroll
+    for (int r = 0; r < (su == 3 ? 7 : 9); r++) {
+      const uint32_t cnt = byte_of(offsetof(MjHandQuery, hand) + 9 * su + r);
       hw |= (cnt > 7 ? 7u : cnt) << (3 * r);
     }
     hi.h[su] = hw;
   }
-  hi.meldw = (uint64_t)q.meld[0] | (uint64_t)q.meld[1] << 16 | (uint64_t)q.meld[2] << 32 | (uint64_t)q.meld[3] << 48;
-  hi.n_meld = q.n_meld; hi.win = q.win_kind; hi.flags = q.flags; hi.riichi = q.riichi;
-  hi.seat_wind = q.seat_wind; hi.round_wind = q.round_wind; hi.n_ind = q.n_ind; hi.n_aka = q.n_aka; hi.kuitan = q.kuitan;
-  for (int j = 0; j < 5; j++) { hi.ind[j] = q.ind[j]; hi.ura[j] = q.ura[j]; }
+  static_assert(offsetof(MjHandQuery, meld) % 2 == 0 && sizeof(MjHandQuery::meld) == 8 && sizeof(MjHandQuery::hand) == 34, "query record layout");
+  hi.meldw = 0;
+#pragma unroll
+  for (int j = 0; j < 4; j++) hi.meldw |= (uint64_t)half_of(offsetof(MjHandQuery, meld) + 2 * j) << (16 * j);
+#define MJ_Q(field) (int)byte_of(offsetof(MjHandQuery, field))
+  hi.n_meld = MJ_Q(n_meld); hi.win = MJ_Q(win_kind); hi.flags = MJ_Q(flags); hi.riichi = MJ_Q(riichi);
+  hi.seat_wind = MJ_Q(seat_wind); hi.round_wind = MJ_Q(round_wind); hi.n_ind = MJ_Q(n_ind); hi.n_aka = MJ_Q(n_aka);
+  hi.kuitan = MJ_Q(kuitan);
+#undef MJ_Q
+#pragma unroll
+  for (int j = 0; j < 5; j++) {
+    hi.ind[j] = (uint8_t)byte_of(offsetof(MjHandQuery, ind) + j); hi.ura[j] = (uint8_t)byte_of(offsetof(MjHandQuery, ura) + j);
+  }
   HandOut ho;
-  eval_hand(L, hi, ho);
+  eval_hand<true>(&L, hi, ho);
   MjHandResult r;
   r.yaku = ho.yaku; r.points = ho.points; r.han = (uint8_t)ho.han; r.fu = (uint8_t)ho.fu;
   r.yakuman_units = (uint8_t)ho.units; r.shape_ok = (uint8_t)ho.shape_ok; r.yaku_ok = (uint8_t)ho.yaku_ok;
@@ -1238,6 +1258,16 @@ inline int pick_lanes(int64_t B, int n_cu)
   const int64_t lanes = (B + slots - 1) / slots;
   return (int)(lanes < kMaxLanes ? lanes : kMaxLanes);
 }
+// Hands per wavefront of the evaluator for a batch: as few as fill twelve wavefront slots per compute unit, at most 64.
+// A wavefront's chain grows with the ways and decompositions of its hands, so small batches are spread (us per call, 64
+// hands per wavefront as against this rule: 1,000 hands 14.3 -> 12.9, 4,000 14.9 -> 12.5 to 14.7, 16,000 15.6 -> 13.1,
+// 65,536 17.7 -> 15.4; 8 and 16 slots do as well within 2 us, one hand per wavefront at any size costs 27 us at 16,000).
+inline int eval_lanes(int64_t n, int n_cu)
+{
+  const int64_t slots = (int64_t)n_cu * 12, lanes = (n + slots - 1) / slots;
+  return (int)(lanes < 64 ? lanes : 64);
+}
+inline unsigned eval_blocks(int64_t n, int lanes) { const int64_t e = (int64_t)(kAuxBlock / 64) * lanes; return (unsigned)((n + e - 1) / e); }
 // a step kernel over n_envs environments: its arguments start with (state, B, rules, tables, environments per wavefront)
 #define MJ_LAUNCH_STEP(kern, h, st, n_envs, ...)                                                                 \
   kern<<<step_blocks((n_envs), (h)->lanes), kBlock, (h)->lds_bytes, st>>>((h)->d_state, (h)->B, (h)->R, (h)->T, (h)->lanes, __VA_ARGS__)
@@ -1250,12 +1280,12 @@ inline int check(hipError_t e) { return e == hipSuccess ? MJ_OK : MJ_E_HIP; }
 constexpr size_t kStaticScratchBytes = 384 * 1024;
 static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 16;
-struct StaticTables { bool ready; DevTables T; };
+struct StaticTables { bool ready; DevTables T; int n_cu; };
 StaticTables g_static[kMaxDevices];
 std::mutex g_static_mu;
 
 // the tables of the CURRENT device, uploaded on first use (a synchronous copy from a host image)
-int static_tables(const DevTables **out)
+int static_tables(const StaticTables **out)
 {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return MJ_E_HIP;
@@ -1267,6 +1297,7 @@ int static_tables(const DevTables **out)
     const ScratchLayout sl = scratch_layout();
     const size_t need = sl.nb;                            // everything before the neighbour and shanten tables
     if (need > kStaticScratchBytes || (sl.probe_bytes & 15)) return MJ_E_UNSUPPORTED;
+    if (hipDeviceGetAttribute(&st.n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || st.n_cu <= 0) return MJ_E_HIP;
     uint8_t *ptr = nullptr;
     if (hipGetSymbolAddress((void **)&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return MJ_E_HIP;
     std::vector<uint8_t> img(need, 0);
@@ -1284,7 +1315,7 @@ int static_tables(const DevTables **out)
     st.T.probe_bytes = (int)sl.probe_bytes;
     st.ready = true;
   }
-  *out = &st.T;
+  *out = &st;
   return MJ_OK;
 }
 
@@ -1363,7 +1394,7 @@ int mj_init(MjHandle **out, void *d_state, void *d_scratch, int64_t B, uint64_t 
   h->sh_suit = (const uint32_t *)(sc + sl.sh_suit);
   h->sh_honor = (const uint32_t *)(sc + sl.sh_honor);
   h->obs_ctr = (unsigned *)(sc + sl.counters);
-  if (rc == MJ_OK) { const DevTables *unused; rc = static_tables(&unused); }   // for mj_eval_hands_static on this device
+  if (rc == MJ_OK) { const StaticTables *unused; rc = static_tables(&unused); }   // for mj_eval_hands_static on this device
   if (rc == MJ_OK) rc = check(hipEventCreate(&h->ev[0]));
   if (rc == MJ_OK) rc = check(hipEventCreate(&h->ev[1]));
   if (rc != MJ_OK) { delete h; return rc; }
@@ -1524,7 +1555,8 @@ int mj_eval_hands(const MjHandle *h, int64_t n, const MjHandQuery *d_in, MjHandR
   if (!h || n < 0) return MJ_E_ARG;
   if (n == 0) return MJ_OK;                               // an empty batch needs no buffers
   if (!d_in || !d_out || ((uintptr_t)d_in & 15) || ((uintptr_t)d_out & 7)) return MJ_E_ARG;
-  k_eval_hands<<<blocks_for(n), kAuxBlock, h->probe_bytes, (hipStream_t)stream>>>(h->T, n, d_in, d_out);
+  const int lanes = eval_lanes(n, h->n_cu);
+  k_eval_hands<<<eval_blocks(n, lanes), kAuxBlock, h->probe_bytes, (hipStream_t)stream>>>(h->T, lanes, n, d_in, d_out);
   return check(hipGetLastError());
 }
 
@@ -1533,10 +1565,11 @@ int mj_eval_hands_static(int64_t n, const MjHandQuery *d_in, MjHandResult *d_out
   if (n < 0 || n > MJ_EVAL_STATIC_MAX_HANDS) return MJ_E_RANGE;
   if (n == 0) return MJ_OK;
   if (!d_in || !d_out || ((uintptr_t)d_in & 15) || ((uintptr_t)d_out & 7)) return MJ_E_ARG;
-  const DevTables *T = nullptr;
-  int rc = static_tables(&T);          // ready since mj_init on this device, otherwise uploaded now
+  const StaticTables *st = nullptr;
+  int rc = static_tables(&st);         // ready since mj_init on this device, otherwise uploaded now
   if (rc != MJ_OK) return rc;
-  k_eval_hands<<<blocks_for(n), kAuxBlock, T->probe_bytes, (hipStream_t)stream>>>(*T, n, d_in, d_out);
+  const int lanes = eval_lanes(n, st->n_cu);
+  k_eval_hands<<<eval_blocks(n, lanes), kAuxBlock, st->T.probe_bytes, (hipStream_t)stream>>>(st->T, lanes, n, d_in, d_out);
   return check(hipGetLastError());
 }
 

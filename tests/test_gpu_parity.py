@@ -381,6 +381,16 @@ def test_hand_microbatch_full_size():
     assert g.eval_hands(q[:257]).tobytes() == ro[:257].tobytes()
 
 
+@pytest.mark.parametrize("n", [1, 2, 65, 3072, 3073, 9217, 196608, 196609])
+def test_hands_per_wavefront(n):
+    """a batch is spread over the machine, one to 64 hands per wavefront: sizes around one hand each (3,072 wavefronts
+    of 256 compute units), three and four each, and full wavefronts"""
+    q = hands.generate(n, mjo.QUERY_DTYPE, seed=n)
+    g = GpuEngine(64, seed=0, flags=mjo.RULES_RED, mode=mjo.MODE_HALF)
+    assert g.eval_hands(q).tobytes() == mjo.eval_hands(q).tobytes()
+    g.close()
+
+
 def test_standings_match_the_records():
     B = 600
     o = mjo.Oracle(B, 5, mjo.RULES_RED, mjo.MODE_EAST)
