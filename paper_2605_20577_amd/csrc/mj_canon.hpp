@@ -234,18 +234,28 @@ MJ_HD void tok_own(const Env &e, int me, const uint32_t *sh_suit, const uint32_t
   const uint32_t swm = e.seatw[me * n];
   uint32_t h[4];
   for (int su = 0; su < 4; su++) h[su] = e.hand[(me * 4 + su) * n];
-  int cnt = 0;
+  // fourteen slots in turn, every lane in step: k = the kind at hand, c = copies of it still to be written
+  uint64_t left = 0;
+  int tiles = 0;
   for (int su = 0; su < 4; su++) {
-    const int nr = su == 3 ? 7 : 9;
-    for (int r = 0; r < nr; r++) {
-      int c = cnt3(h[su], r);
-      const int k = (su == 3 ? 27 : 9 * su) + r;
-      if (su < 3 && r == 4 && (swm >> su & 1u) && c > 0) { if (cnt < 14) o.hand[cnt] = tile_token(k, 1); cnt++; c--; }
-      for (int i = 0; i < c; i++) { if (cnt < 14) o.hand[cnt] = tile_token(k, 0); cnt++; }
-    }
+    const uint32_t w = h[su] & (su == 3 ? 0x1FFFFFu : 0x7FFFFFFu);
+    left |= (uint64_t)squeeze9(fields_nonzero(w)) << (9 * su);
+    tiles += tiles_in(w);
   }
-  for (int i = cnt; i < 14; i++) o.hand[i] = 255;
-  o.n_hand = (uint8_t)cnt;
+  int k = 0, c = 0, red = 0;
+#pragma unroll 1
+  for (int i = 0; i < 14; i++) {
+    if (c == 0 && left) {
+      k = ctz64(left);
+      left &= left - 1;
+      c = hand_count(h, k);
+      red = is_five(k) ? (int)(swm >> (k / 9) & 1u) : 0;
+    }
+    o.hand[i] = c ? tile_token(k, red) : (uint8_t)255;
+    red = 0;
+    c -= c ? 1 : 0;
+  }
+  o.n_hand = (uint8_t)tiles;
   o.shanten = (int8_t)shanten_of(sh_suit, sh_honor, h[0], h[1], h[2], h[3], (int)sw_get(swm, SW_NMELD, 3));
 }
 // the game's scalars as the viewer sees them

@@ -1092,26 +1092,29 @@ __global__ void __launch_bounds__(kAuxBlock) k_observe(void *state, int64_t B, u
 }
 
 // Token observation.  One lane per (environment, seat).  What the four viewers of a game share is computed once:
-// lane (env, s) turns seat s's river into token bytes in LDS; as viewer s, it writes the first 96 bytes of its record
-// (own hand, shanten number, scalars, the seats' words rotated to it) into LDS, and stages a quarter of the game's
-// action history (two entries per word, absolute
-// seats).  The block then streams the records out, one record per wavefront and iteration, consecutive lanes on
-// consecutive words: 24 words from the record head, 32 from the four rivers picked by relative seat, 4 for the
-// length of the history, 64 of history with the seats turned to the viewer.
+// lane (env, s) turns seat s's river into token bytes in LDS and, as viewer s, writes the first 96 bytes of its record
+// (own hand, shanten number, scalars, the seats' words rotated to it) into LDS.  The block then streams the records
+// out: a wavefront takes sixteen games, two at a time, and each half of it writes a game's four records of 31 chunks of
+// 16 bytes (6 from the record head, 8 from the four rivers picked by relative seat, 1 with the length of the history, 16
+// of history with the seats turned to the viewer), lane by lane on consecutive addresses.  The history goes from its row
+// to registers, 16 bytes per lane of one contiguous run, once for the four viewers.
+// Bound by its stores and by the one round of loads before them (1,024 blocks of 65,536 games fit the machine at once,
+// four per compute unit; with the history in LDS only three did).  65,536 games 56.6 -> 44.6 us, 262,144 games 159 -> 147
+// us (3.8 TB/s); the viewers' loop is rolled because code is read cold in every launch (unrolled: 48.1 us).
 constexpr int kTokEnvs = kAuxBlock / 4;           // 64 environments per block
 constexpr int kTokHead = 96;                      // bytes of MjTokenObs before river[][]
 constexpr int kTokHeadStride = 100, kTokRivStride = 36;   // LDS strides: an odd number of words, so that the lanes of a
                                                           // wavefront (consecutive environments) fall into different banks
-constexpr int kTokHistStride = 65;                // words per game in the LDS copy of the history (odd, as above)
 static_assert(offsetof(MjTokenObs, river) == kTokHead && offsetof(MjTokenObs, n_hist) == kTokHead + 128 &&
               offsetof(MjTokenObs, hist) == kTokHead + 144 && sizeof(MjTokenObs) == kTokHead + 144 + 256, "token record layout");
-__global__ void __launch_bounds__(kAuxBlock) k_observe_tokens(void *state, int64_t B, uint32_t rule_flags, const uint32_t *sh_suit,
-                                                           const uint32_t *sh_honor, MjTokenObs *out)
+__global__ void __launch_bounds__(kAuxBlock, 4) k_observe_tokens(void *state, int64_t B, uint32_t rule_flags, const uint32_t *sh_suit,
+                                                              const uint32_t *sh_honor, MjTokenObs *out)
 {
-  __shared__ __align__(4) uint8_t head[4][kTokEnvs][kTokHeadStride];       // [viewer][env]
-  __shared__ __align__(4) uint8_t riv[4][kTokEnvs][kTokRivStride];         // [seat][env]
-  __shared__ uint32_t p_hist[kTokEnvs][kTokHistStride];                    // two entries per word: action | seat << 8
-  __shared__ uint32_t p_nhist[kTokEnvs];
+  __shared__ struct TokShared {
+    __align__(4) uint8_t head[4][kTokEnvs][kTokHeadStride];       // [viewer][env]
+    __align__(4) uint8_t riv[4][kTokEnvs][kTokRivStride];         // [seat][env]
+    uint32_t nhist[kTokEnvs];
+  } M;
   const int tid = threadIdx.x;
   const int64_t base = (int64_t)blockIdx.x * kTokEnvs;
   const int nenv = (int)((B - base) < kTokEnvs ? (B - base) : kTokEnvs);
@@ -1120,11 +1123,10 @@ __global__ void __launch_bounds__(kAuxBlock) k_observe_tokens(void *state, int64
   const bool on = tid < 4 * nenv;
   Env e = make_env(state, B, base + (on ? el : 0));
   // MjTokenObs is used as a view of the record head only: nothing below touches river[][]
-  MjTokenObs &o = *(MjTokenObs *)head[on ? s : 0][on ? el : 0];
+  MjTokenObs &o = *(MjTokenObs *)M.head[on ? s : 0][on ? el : 0];
   if (on) {
-    tok_river(e, s, riv[s][el]);
-    // the four seats' public words, read by each of the game's four lanes (the repeats are cache hits): 52 KB of LDS
-    // instead of 56 KB lets three blocks share a compute unit
+    tok_river(e, s, M.riv[s][el]);
+    // the four seats' public words, read by each of the game's four lanes (the repeats are cache hits)
     uint32_t sw[4];
     int32_t sc[4];
     uint64_t ml[4];
@@ -1134,49 +1136,62 @@ __global__ void __launch_bounds__(kAuxBlock) k_observe_tokens(void *state, int64
     load_glob(e, g);
     tok_own(e, s, sh_suit, sh_honor, o);
     tok_env(e, g, s, rule_flags, o);
-    // entries 32 s .. 32 s + 31 of the history: sixteen words of the environment's row, two entries each
-    const int nh = g.hist_len;
-    if (s == 0) p_nhist[el] = (uint32_t)nh;
-    uint32_t hv[16];
-#pragma unroll
-    for (int j = 0; j < 16; j++) hv[j] = row_word(e.hist + 32 * s, j);              // all sixteen loads in flight together
-#pragma unroll
-    for (int j = 0; j < 16; j++) {
-      const int i0 = 32 * s + 2 * j;
-      const uint32_t lo = i0 < nh ? hv[j] & 0xFFFFu : 0xFFFFu, hi = i0 + 1 < nh ? hv[j] >> 16 : 0xFFFFu;
-      p_hist[el][16 * s + j] = lo | hi << 16;
-    }
+    if (s == 0) M.nhist[el] = (uint32_t)g.hist_len;
     tok_seats(sw, sc, ml, s, o);
   }
+  static_assert(sizeof(MjTokenObs) == 31 * 16 && kAuxBlock / 64 == 4 && kTokEnvs == 64, "token record chunks");
+  const int ch = tid & 31, first = 16 * (tid >> 6) + (tid >> 5 & 1);        // this lane's chunk, its half's first game
+  const bool live = ch < 31, is_len = ch == 14, is_hist = ch > 14 && live;
+  u32x4 hv[8];
+  const uint16_t *rows = make_env(state, B, base).hist;
+#pragma unroll
+  for (int it = 0; it < 8; it++) {
+    const int env = first + 2 * it;
+    u32x4 x = {0u, 0u, 0u, 0u};
+    if (is_hist && env < nenv) {
+      const uint16_t *row = rows + (size_t)env * 128 + 8 * (ch - 15);
+#pragma unroll
+      for (int j = 0; j < 4; j++) x[j] = row_word(row, j);
+    }
+    hv[it] = x;
+  }
   __syncthreads();
-  // out: wavefront `me` writes the records of viewer `me`, two games per iteration; each half of the wavefront streams
-  // one record of 31 chunks of 16 bytes (6 from the record head, 8 from the four rivers picked by relative seat, 1 with
-  // the length of the history, 16 of history), lane by lane on consecutive addresses; a lane's source is a fixed LDS
-  // address plus a stride per game
-  static_assert(sizeof(MjTokenObs) == 31 * 16 && kAuxBlock / 64 == 4, "token record chunks");
-  const int lane = tid & 63, me = tid >> 6, ch = lane & 31;
-  const bool live = ch < 31, is_len = ch == 14, is_hist = ch > 14;
-  const uint8_t *src = &head[me][0][16 * (ch < 6 ? ch : 0)];
-  int stride = kTokHeadStride;
-  if (ch >= 6 && ch < 14) { src = &riv[(me + ((ch - 6) >> 1)) & 3][0][16 * ((ch - 6) & 1)]; stride = kTokRivStride; }
-  if (is_hist && live) { src = (const uint8_t *)&p_hist[0][4 * (ch - 15)]; stride = 4 * kTokHistStride; }
-  // a history word as this viewer sees it: seats turned, unused entries left at 0xFFFF
-  const uint32_t sub = 0x00040004u - (uint32_t)me * 0x00010001u;
-  auto turned = [&](uint32_t x) {
-    uint32_t y = (x & 0x00FF00FFu) | (((x >> 8 & 0x00030003u) + sub) & 0x00030003u) << 8;
-    if ((x & 0xFFu) == 0xFFu) y |= 0x0000FFFFu;
-    if ((x >> 16 & 0xFFu) == 0xFFu) y |= 0xFFFF0000u;
-    return y;
-  };
-  u32x4 *dst = (u32x4 *)(out + base * 4 + me) + ch;
-#pragma unroll 2
-  for (int env = lane >> 5; env < nenv; env += 2) {
-    const uint32_t *p = (const uint32_t *)(src + env * stride);
-    u32x4 v;
-    v.x = p[0]; v.y = p[1]; v.z = p[2]; v.w = p[3];
-    if (is_hist) { v.x = turned(v.x); v.y = turned(v.y); v.z = turned(v.z); v.w = turned(v.w); }
-    if (is_len) { v.x = p_nhist[env]; v.y = 0u; v.z = 0u; v.w = 0u; }
-    if (live) __builtin_nontemporal_store(v, dst + (size_t)env * (4 * sizeof(MjTokenObs) / 16));
+  // where this lane's chunk of viewer me's record comes from: a river word of seat (me + rel) & 3, or of the head
+  // (history and length lanes read, and drop, the head)
+  const bool is_riv = ch >= 6 && ch < 14;
+  const uint8_t *src = is_riv ? &M.riv[0][0][16 * ((ch - 6) & 1)] : &M.head[0][0][16 * (ch < 6 ? ch : 0)];
+  const int stride = is_riv ? kTokRivStride : kTokHeadStride, seat0 = is_riv ? (ch - 6) >> 1 : 0;
+  u32x4 *dst = (u32x4 *)(out + base * 4) + ch;
+#pragma unroll
+  for (int it = 0; it < 8; it++) {
+    const int env = first + 2 * it;
+    if (env < nenv) {
+      const int nh = (int)M.nhist[env];
+      u32x4 hx = hv[it];
+#pragma unroll
+      for (int j = 0; j < 4; j++) {                    // entries behind the end are 0xFFFF ...
+        const int i0 = 8 * (ch - 15) + 2 * j;
+        hx[j] |= (i0 < nh ? 0u : 0xFFFFu) | (i0 + 1 < nh ? 0u : 0xFFFF0000u);
+      }
+#pragma unroll 1
+      for (int me = 0; me < 4; me++) {
+        const uint32_t *p = (const uint32_t *)(src + (((seat0 + me) & 3) * kTokEnvs + env) * stride);
+        u32x4 v;
+        v.x = p[0]; v.y = p[1]; v.z = p[2]; v.w = p[3];
+        if (is_hist) {
+          const uint32_t sub = 0x00040004u - (uint32_t)me * 0x00010001u;
+#pragma unroll
+          for (int j = 0; j < 4; j++) {                // ... and stay that; the seats of the others are turned to the viewer
+            uint32_t y = (hx[j] & 0x00FF00FFu) | (((hx[j] >> 8 & 0x00030003u) + sub) & 0x00030003u) << 8;
+            if ((hx[j] & 0xFFu) == 0xFFu) y |= 0x0000FFFFu;
+            if ((hx[j] >> 16 & 0xFFu) == 0xFFu) y |= 0xFFFF0000u;
+            v[j] = y;
+          }
+        }
+        if (is_len) { v.x = (uint32_t)nh; v.y = 0u; v.z = 0u; v.w = 0u; }
+        if (live) __builtin_nontemporal_store(v, dst + ((size_t)env * 4 + me) * (sizeof(MjTokenObs) / 16));
+      }
+    }
   }
 }
 

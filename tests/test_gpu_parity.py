@@ -486,6 +486,21 @@ def test_token_observation(B, flags, mode):
         assert {-1, 0, 1, 2, 3, 4, 5} <= shanten_seen
 
 
+@pytest.mark.parametrize("B", [2, 63, 64, 65, 191, 1027])
+def test_token_records_of_part_filled_blocks(B):
+    """blocks of 64 games, sixteen per wavefront, two at a time: batches that leave halves, wavefronts and blocks part
+    empty, with short and long histories"""
+    o = mjo.Oracle(B, 29, mjo.RULES_RED, mjo.MODE_HALF)
+    g = GpuEngine(B, seed=29, flags=mjo.RULES_RED, mode=mjo.MODE_HALF)
+    for n in (0, 1, 37, 300):
+        o.step_random(n); g.step_random(n)
+        want = o.observe_tokens()
+        got = g.env.observe_tokens().cpu().numpy().reshape(B, 4, -1).view(mjo.TOKEN_DTYPE).reshape(B, 4)
+        for name in want.dtype.names:
+            assert np.array_equal(want[name], got[name]), (n, name)
+    g.close()
+
+
 def test_binding_refuses_tensors_the_kernels_could_not_index():
     """a caller's tensor of the wrong size, dtype or device is refused on the host, before any launch"""
     import torch
