@@ -930,23 +930,27 @@ constexpr int kObsEnvs = 32;             // 49 KB of LDS per block; 16 per group
 constexpr int kObsBits = 56 * 34;                 // 1904
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kObsWords = 60;                     // u32 words per (env, viewer), 1920 bits
-constexpr int kObsStride = 33;                    // elements between two rows of the raw copy in LDS
 constexpr int kObsRawRows = 35;                   // u32 rows: seat words 0..3, hands 4..19, scores 20..23, control 24..30,
                                                   // wall words 31, 32 of buffer 0 and of buffer 1: 31..34
-struct ObsRaw {
-  uint64_t meld[4][kObsStride];
-  uint32_t w[kObsRawRows][kObsStride];
-  uint8_t river[128][kObsStride];
+// E = environments per group, a power of two from 4 to 32; rows of the raw copy in LDS are E + 1 elements apart
+template <int E> struct ObsRaw {
+  uint64_t meld[4][E + 1];
+  uint32_t w[kObsRawRows][E + 1];
+  uint8_t river[128][E + 1];
 };
 // what one lane holds of a group between its loads and their way into LDS
-struct ObsFetch { uint32_t w[5]; uint64_t meld; uint32_t riv[4]; };
+template <int E> struct ObsFetch {
+  static constexpr int kWords = (kObsRawRows * E + kAuxBlock - 1) / kAuxBlock, kRivers = (128 * E / 4 + kAuxBlock - 1) / kAuxBlock;
+  uint32_t w[kWords]; uint64_t meld; uint32_t riv[kRivers];
+};
 
-__device__ __forceinline__ void obs_fetch(void *state, int64_t B, int64_t base, int nenv, int tid, ObsFetch &f)
+template <int E> __device__ __forceinline__ void obs_fetch(void *state, int64_t B, int64_t base, int nenv, int tid, ObsFetch<E> &f)
 {
   const Env e = make_env(state, B, base);
+  constexpr int Q = E / 4;                         // words of four river bytes per row
 #pragma unroll
-  for (int k = 0; k < 5; k++) {
-    const int idx = tid + kAuxBlock * k, r = idx >> 5, el = idx & 31;
+  for (int k = 0; k < ObsFetch<E>::kWords; k++) {
+    const int idx = tid + kAuxBlock * k, r = idx / E, el = idx % E;
     const uint32_t *row = r < 4    ? e.seatw + (int64_t)r * B
                           : r < 20 ? e.hand + (int64_t)(r - 4) * B
                           : r < 24 ? (const uint32_t *)e.score + (int64_t)(r - 20) * B
@@ -954,91 +958,95 @@ __device__ __forceinline__ void obs_fetch(void *state, int64_t B, int64_t base, 
                                    : e.wallw + (int64_t)(((r - 31) >> 1) * 34 + 31 + ((r - 31) & 1)) * B;
     f.w[k] = (r < kObsRawRows && el < nenv) ? row[el] : 0u;
   }
-  f.meld = (tid < 128 && (tid & 31) < nenv) ? e.meld[(int64_t)(tid >> 5) * B + (tid & 31)] : 0ull;
+  f.meld = (tid < 4 * E && tid % E < nenv) ? e.meld[(int64_t)(tid / E) * B + tid % E] : 0ull;
   if ((B & 3) == 0) {
     // rows start on a word boundary, and a group that is not full still has a multiple of four environments
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-      const int idx = tid + kAuxBlock * k, r = idx >> 3, q = idx & 7;
-      f.riv[k] = 4 * q < nenv ? *(const uint32_t *)(e.river + (int64_t)r * B + 4 * q) : 0xFFFFFFFFu;
+    for (int k = 0; k < ObsFetch<E>::kRivers; k++) {
+      const int idx = tid + kAuxBlock * k, r = idx / Q, q = idx % Q;
+      f.riv[k] = (r < 128 && 4 * q < nenv) ? *(const uint32_t *)(e.river + (int64_t)r * B + 4 * q) : 0xFFFFFFFFu;
     }
   } else {
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-      const int idx = tid + kAuxBlock * k, r = idx >> 3, q = idx & 7;
+    for (int k = 0; k < ObsFetch<E>::kRivers; k++) {
+      const int idx = tid + kAuxBlock * k, r = idx / Q, q = idx % Q;
       uint32_t v = 0;
 #pragma unroll
-      for (int j = 0; j < 4; j++) v |= (uint32_t)(4 * q + j < nenv ? e.river[(int64_t)r * B + 4 * q + j] : 255) << (8 * j);
+      for (int j = 0; j < 4; j++) v |= (uint32_t)(r < 128 && 4 * q + j < nenv ? e.river[(int64_t)r * B + 4 * q + j] : 255) << (8 * j);
       f.riv[k] = v;
     }
   }
 }
-__device__ __forceinline__ void obs_commit(ObsRaw &raw, int tid, const ObsFetch &f)
+template <int E> __device__ __forceinline__ void obs_commit(ObsRaw<E> &raw, int tid, const ObsFetch<E> &f)
 {
+  constexpr int Q = E / 4;
 #pragma unroll
-  for (int k = 0; k < 5; k++) {
-    const int idx = tid + kAuxBlock * k, r = idx >> 5, el = idx & 31;
+  for (int k = 0; k < ObsFetch<E>::kWords; k++) {
+    const int idx = tid + kAuxBlock * k, r = idx / E, el = idx % E;
     if (r < kObsRawRows) raw.w[r][el] = f.w[k];
   }
-  if (tid < 128) raw.meld[tid >> 5][tid & 31] = f.meld;
+  if (tid < 4 * E) raw.meld[tid / E][tid % E] = f.meld;
 #pragma unroll
-  for (int k = 0; k < 4; k++) {
-    const int idx = tid + kAuxBlock * k, r = idx >> 3, q = idx & 7;
+  for (int k = 0; k < ObsFetch<E>::kRivers; k++) {
+    const int idx = tid + kAuxBlock * k, r = idx / Q, q = idx % Q;
+    if (r >= 128) continue;
 #pragma unroll
     for (int j = 0; j < 4; j++) raw.river[r][4 * q + j] = (uint8_t)(f.riv[k] >> (8 * j));
   }
 }
 // view of environment el of the raw copy, for the code that reads a state through an Env
-__device__ __forceinline__ Env obs_view(ObsRaw &raw, int el)
+template <int E> __device__ __forceinline__ Env obs_view(ObsRaw<E> &raw, int el)
 {
   Env v = {};
-  v.n = kObsStride; v.hs = kObsStride;
+  v.n = E + 1; v.hs = E + 1;
   v.seatw = &raw.w[0][el]; v.hand = &raw.w[4][el]; v.score = (int32_t *)&raw.w[20][el]; v.glob = &raw.w[24][el];
   v.meld = &raw.meld[0][el]; v.river = &raw.river[0][el];
   return v;
 }
 
-__global__ void __launch_bounds__(kAuxBlock) k_observe(void *state, int64_t B, uint32_t rule_flags, uint8_t *obs, unsigned *ctr)
+template <int E> __global__ void __launch_bounds__(kAuxBlock) k_observe(void *state, int64_t B, uint32_t rule_flags, uint8_t *obs, unsigned *ctr)
 {
-  __shared__ uint64_t S[kObsEnvs][4][OB_SEAT_WORDS];
-  __shared__ uint64_t G[kObsEnvs][OG_WORDS];
-  __shared__ uint64_t R[kObsEnvs][4];
-  __shared__ uint32_t own_red[kObsEnvs][4];
-  __shared__ union ObsShared { uint32_t bits[kObsEnvs][4][kObsWords]; ObsRaw raw; } U;   // raw is dead once S and G are made
+  __shared__ uint64_t S[E][4][OB_SEAT_WORDS];
+  __shared__ uint64_t G[E][OG_WORDS];
+  __shared__ uint64_t R[E][4];
+  __shared__ uint32_t own_red[E][4];
+  __shared__ union ObsShared { uint32_t bits[E][4][kObsWords]; ObsRaw<E> raw; } U;   // raw is dead once S and G are made
   __shared__ unsigned next_group;
-  static_assert(sizeof(ObsRaw) <= sizeof(uint32_t) * kObsEnvs * 4 * kObsWords, "the raw copy fits under the bit strings");
+  static_assert( sizeof(ObsRaw<E>) <= sizeof(uint32_t) * E * 4 * kObsWords, "the raw copy fits under the bit strings");
   const int tid = threadIdx.x;
-  const int64_t n_groups = (B + kObsEnvs - 1) / kObsEnvs;
-  // The counter's value g stands for environments (n_groups - 1 - g) * 32 ..: from the end of the batch down, so that a
+  const int64_t n_groups = (B + E - 1) / E;
+  // The counter's value g stands for environments (n_groups - 1 - g) * E ..: from the end of the batch down, so that a
   // launch that follows a step starts with the environments that the step wrote last (what the memory-side cache
   // still holds): 1.60 -> 1.57 ms at B = 2^20.
-  if (tid == 0) next_group = atomicAdd(&ctr[0], 1u);
-  __syncthreads();
-  int64_t grp = next_group;
-  ObsFetch f;
+  // A block's first group is its own number and the counter hands out those after the grid's, so a launch whose blocks
+  // have one group each touches no counter: on one address atomics of all compute units go one after the other (250
+  // blocks of four games: 27 us with them, 14 without; 65,536 games in groups of 32: 123 -> 115 us).
+  const bool queued = n_groups > (int64_t)gridDim.x;
+  int64_t grp = blockIdx.x;
+  ObsFetch<E> f;
   if (grp < n_groups) {
-    const int64_t base = (n_groups - 1 - grp) * kObsEnvs;
-    obs_fetch(state, B, base, (int)((B - base) < kObsEnvs ? (B - base) : kObsEnvs), tid, f);
+    const int64_t base = (n_groups - 1 - grp) * E;
+    obs_fetch<E>(state, B, base, (int)((B - base) < E ? (B - base) : E), tid, f);
   }
   while (grp < n_groups) {
-    const int64_t base = (n_groups - 1 - grp) * kObsEnvs;
-    const int nenv = (int)((B - base) < kObsEnvs ? (B - base) : kObsEnvs);
+    const int64_t base = (n_groups - 1 - grp) * E;
+    const int nenv = (int)((B - base) < E ? (B - base) : E);
     unsigned taken = 0;
-    if (tid == 0) taken = atomicAdd(&ctr[0], 1u);      // the group after this one; its answer is needed only below
-    obs_commit(U.raw, tid, f);
+    if (queued && tid == 0) taken = atomicAdd(&ctr[0], 1u);      // the group after this one; its answer is needed only below
+    obs_commit<E>(U.raw, tid, f);
     __syncthreads();
     if (tid < 4 * nenv) {
       int el = tid >> 2, s = tid & 3;
-      Env e = obs_view(U.raw, el);
+      Env e = obs_view<E>(U.raw, el);
       uint64_t m[OB_SEAT_WORDS];
       R[el][s] = obs_seat_masks(e, s, m);
 #pragma unroll
       for (int i = 0; i < OB_SEAT_WORDS; i++) S[el][s][i] = m[i];
-      own_red[el][s] = e.seatw[s * kObsStride] & 7u;
+      own_red[el][s] = e.seatw[s * (E + 1)] & 7u;
     }
     __syncthreads();
     if (tid < nenv) {
-      Env e = obs_view(U.raw, tid);
+      Env e = obs_view<E>(U.raw, tid);
       Glob g;
       load_glob(e, g);
       const uint32_t dw[2] = {U.raw.w[31 + 2 * g.wall_sel][tid], U.raw.w[32 + 2 * g.wall_sel][tid]};
@@ -1048,25 +1056,38 @@ __global__ void __launch_bounds__(kAuxBlock) k_observe(void *state, int64_t B, u
       for (int i = 0; i < OG_WORDS; i++) G[tid][i] = m[i];
     }
     __syncthreads();
-    if (tid < 4 * nenv) {
-      int el = tid >> 2, me = tid & 3;
-      uint32_t *out = U.bits[el][me];
-      uint64_t acc = 0;
-      int fill = 0, wpos = 0;                 // fill stays even and <= 30 before each plane is added
-      for (int p = 0; p < 56; p++) {
-        uint64_t v = obs_plane(p, me, &S[el][0][0], own_red[el][me], G[el]) & K_ALL;
-        acc |= v << fill;
-        fill += 34;
-        while (fill >= 32) { out[wpos++] = (uint32_t)acc; acc >>= 32; fill -= 32; }
+    if constexpr (E == kObsEnvs) {
+      if (tid < 4 * nenv) {
+        int el = tid >> 2, me = tid & 3;
+        uint32_t *out = U.bits[el][me];
+        uint64_t acc = 0;
+        int fill = 0, wpos = 0;                 // fill stays even and <= 30 before each plane is added
+        for (int p = 0; p < 56; p++) {
+          uint64_t v = obs_plane(p, me, &S[el][0][0], own_red[el][me], G[el]) & K_ALL;
+          acc |= v << fill;
+          fill += 34;
+          while (fill >= 32) { out[wpos++] = (uint32_t)acc; acc >>= 32; fill -= 32; }
+        }
+        while (wpos < kObsWords) { out[wpos++] = (uint32_t)acc; acc = 0; }
       }
-      while (wpos < kObsWords) { out[wpos++] = (uint32_t)acc; acc = 0; }
+    } else {
+      // few environments: every lane puts words of the strings together (a word spans at most two planes), so that the
+      // chain is that of eight planes and not of 56
+      for (int i = tid; i < 4 * nenv * kObsWords; i += kAuxBlock) {
+        const int w = i % kObsWords, v = i / kObsWords, el = v >> 2, me = v & 3;
+        const int p = 32 * w / 34, at = 32 * w - 34 * p;                  // the word starts at bit `at` of plane p
+        uint64_t x = 0;
+        if (p < 56) x = (obs_plane(p, me, &S[el][0][0], own_red[el][me], G[el]) & K_ALL) >> at;
+        if (p + 1 < 56) x |= (obs_plane(p + 1, me, &S[el][0][0], own_red[el][me], G[el]) & K_ALL) << (34 - at);
+        U.bits[el][me][w] = (uint32_t)x;
+      }
     }
     if (tid == 0) next_group = taken;
     __syncthreads();
-    const int64_t nxt = next_group;
+    const int64_t nxt = queued ? (int64_t)gridDim.x + next_group : n_groups;
     if (nxt < n_groups) {
-      const int64_t nb = (n_groups - 1 - nxt) * kObsEnvs;
-      obs_fetch(state, B, nb, (int)((B - nb) < kObsEnvs ? (B - nb) : kObsEnvs), tid, f);
+      const int64_t nb = (n_groups - 1 - nxt) * E;
+      obs_fetch<E>(state, B, nb, (int)((B - nb) < E ? (B - nb) : E), tid, f);
     }
     // 7616 bytes per env = 476 stores of 16 bytes; 16 bytes = 16 bits of the string
     const int per_env = 4 * kObsBits / 16;
@@ -1088,7 +1109,7 @@ __global__ void __launch_bounds__(kAuxBlock) k_observe(void *state, int64_t B, u
     grp = nxt;
   }
   // the last block to leave rearms both counters for the next launch
-  if (tid == 0 && atomicAdd(&ctr[1], 1u) == gridDim.x - 1) { atomicExch(&ctr[0], 0u); atomicExch(&ctr[1], 0u); }
+  if (queued && tid == 0 && atomicAdd(&ctr[1], 1u) == gridDim.x - 1) { atomicExch(&ctr[0], 0u); atomicExch(&ctr[1], 0u); }
 }
 
 // Token observation.  One lane per (environment, seat).  What the four viewers of a game share is computed once:
@@ -1099,8 +1120,8 @@ __global__ void __launch_bounds__(kAuxBlock) k_observe(void *state, int64_t B, u
 // of history with the seats turned to the viewer), lane by lane on consecutive addresses.  The history goes from its row
 // to registers, 16 bytes per lane of one contiguous run, once for the four viewers.
 // Bound by its stores and by the one round of loads before them (1,024 blocks of 65,536 games fit the machine at once,
-// four per compute unit; with the history in LDS only three did).  65,536 games 56.6 -> 44.6 us, 262,144 games 159 -> 147
-// us (3.8 TB/s); the viewers' loop is rolled because code is read cold in every launch (unrolled: 48.1 us).
+// four per compute unit; with the history in LDS only three did).  65,536 games 56.6 -> 45 to 47 us, 262,144 games 159 -> 145
+// us; the viewers' loop is rolled because code is read cold in every launch (unrolled: 48.1 us).
 constexpr int kTokEnvs = kAuxBlock / 4;           // 64 environments per block
 constexpr int kTokHead = 96;                      // bytes of MjTokenObs before river[][]
 constexpr int kTokHeadStride = 100, kTokRivStride = 36;   // LDS strides: an odd number of words, so that the lanes of a
@@ -1288,6 +1309,16 @@ inline unsigned eval_blocks(int64_t n, int lanes) { const int64_t e = (int64_t)(
   kern<<<step_blocks((n_envs), (h)->lanes), kBlock, (h)->lds_bytes, st>>>((h)->d_state, (h)->B, (h)->R, (h)->T, (h)->lanes, __VA_ARGS__)
 inline int check(hipError_t e) { return e == hipSuccess ? MJ_OK : MJ_E_HIP; }
 
+// Three blocks fit a compute unit (LDS; smaller groups need less, but are used only where each block has one); they take
+// the groups in order from a counter, so that the blocks in flight write one compact, advancing window
+// of the tensor (measured: 5.8 TB/s against 5.3 TB/s with one block per group in launch order)
+constexpr int64_t kObsResident = 3;
+template <int E> void launch_observe(const MjHandle *h, uint8_t *d_obs, hipStream_t st)
+{
+  const int64_t groups = (h->B + E - 1) / E, resident = kObsResident * h->n_cu;
+  k_observe<E><<<(unsigned)(groups < resident ? groups : resident), kAuxBlock, 0, st>>>(h->d_state, h->B, h->R.flags, d_obs, h->obs_ctr);
+}
+
 // ---- tables for callers that can not allocate (mj_eval_hands_static) ----------------------------------------
 // A copy of the per-suit pattern tables (probe part and records, without the shanten block tables) in a file-scope
 // device array: every GPU the library runs on holds its own copy at its own address until the process ends.  In
@@ -1451,13 +1482,15 @@ int mj_legal_mask(const MjHandle *h, uint64_t *d_mask, void *stream)
 int mj_observe(const MjHandle *h, uint8_t *d_obs, void *stream)
 {
   if (!h || !d_obs || ((uintptr_t)d_obs & 15)) return MJ_E_ARG;
-  int64_t groups = (h->B + kObsEnvs - 1) / kObsEnvs;
-  // three blocks fit a compute unit (LDS); they take the groups of 32 games in order from a counter, so that the
-  // blocks in flight write one compact, advancing window of the tensor (measured: 5.8 TB/s against 5.3 TB/s with
-  // one block per group in launch order)
-  const int64_t resident = (int64_t)h->n_cu * 3;
-  unsigned grid = (unsigned)(groups < resident ? groups : resident);
-  k_observe<<<grid, kAuxBlock, 0, (hipStream_t)stream>>>(h->d_state, h->B, h->R.flags, d_obs, h->obs_ctr);
+  hipStream_t st = (hipStream_t)stream;
+  // Groups of 4 (or 8) games as long as every resident block has one of them, else groups of 32, whose longer runs of
+  // stores a full machine needs: a group is a chain of dependent steps, and 32 games of it leave most compute units idle.
+  // us with groups of 4 / 8 / 32: 100 games 14.2 / 20.6 / 23.6, 1,000: 14.1 / 20.3 / 24.7, 3,001: 17.2 / 22.7 / 27.0,
+  // 4,000: 30.0 / 22.3 / 26.0, 6,000: 40.1 / 23.9 / 25.8, 8,000: 48.9 / 43.3 / 28.1.
+  const int64_t blocks = kObsResident * h->n_cu;
+  if (h->B <= 4 * blocks) launch_observe<4>(h, d_obs, st);
+  else if (h->B <= 8 * blocks) launch_observe<8>(h, d_obs, st);
+  else launch_observe<kObsEnvs>(h, d_obs, st);
   return check(hipGetLastError());
 }
 

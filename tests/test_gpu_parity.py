@@ -127,6 +127,18 @@ def test_observation_more_groups_than_resident_blocks():
     assert np.array_equal(o.observe(), g.observe())
 
 
+@pytest.mark.parametrize("B", [2, 5, 3071, 3074, 6143, 6149, 24579])
+def test_observation_group_sizes(B):
+    """groups of 4, 8 and 32 games: sizes around the changes (3,072 and 6,144 games on 256 compute units) and around the
+    size from which blocks take a second group from the counter (24,576), a part-filled last group each"""
+    o = mjo.Oracle(B, 31, mjo.RULES_RED, mjo.MODE_HALF)
+    g = GpuEngine(B, seed=31, flags=mjo.RULES_RED, mode=mjo.MODE_HALF)
+    for n in (45, 3):
+        o.step_random(n); g.step_random(n)
+        assert np.array_equal(o.observe(), g.observe())
+    g.close()
+
+
 @pytest.mark.parametrize("flags,lpw,seed", [(mjo.RULES_NORED, 32, 3), (mjo.RULES_RED, 64, 4),
                                             (mjo.RULES_RED | mjo.F_ENDGAME | mjo.F_KANDORA_LATE | mjo.F_NAGASHI | mjo.F_ANKAN_ROB | mjo.F_PAO, 32, 5)])
 def test_fused_rollout_large(flags, lpw, seed, monkeypatch):
