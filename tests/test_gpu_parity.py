@@ -393,6 +393,21 @@ def test_hand_microbatch_full_size():
     assert g.eval_hands(q[:257]).tobytes() == ro[:257].tobytes()
 
 
+@pytest.mark.parametrize("B", [1, 65, 131072, 131075])
+def test_sampled_actions(B):
+    """the random policy as a call of its own, a lane per game and seat up to 131,072 games (512 per compute unit), a
+    lane per game beyond"""
+    g = GpuEngine(B, seed=37, flags=mjo.RULES_RED, mode=mjo.MODE_HALF)
+    g.step_random(33)
+    got = g.sample_random()
+    for lo in {0, max(B - 300, 0)}:                  # the first and the last games against an oracle of their own
+        n = min(300, B - lo)
+        o = mjo.Oracle(n, 37, mjo.RULES_RED, mjo.MODE_HALF, env_id_base=lo)
+        o.step_random(33)
+        assert np.array_equal(o.sample_random(), got[lo:lo + n])
+    g.close()
+
+
 @pytest.mark.parametrize("n", [1, 2, 65, 3072, 3073, 9217, 196608, 196609])
 def test_hands_per_wavefront(n):
     """a batch is spread over the machine, one to 64 hands per wavefront: sizes around one hand each (3,072 wavefronts
