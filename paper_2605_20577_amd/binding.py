@@ -127,10 +127,11 @@ def _check(rc):
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p()
+    return t.data_ptr() if t is not None else None          # ctypes turns both into the c_void_p of the argument types
 
 
 _torch = None
+_raw_stream = _cur_device = None
 
 
 def _th():
@@ -143,7 +144,18 @@ def _th():
 
 
 def _stream():
-    return C.c_void_p(_th().cuda.current_stream().cuda_stream)
+    """the current stream of the current device, as its raw handle: torch's Stream object around it costs several
+    microseconds of host time, about as much as the launch itself"""
+    global _raw_stream, _cur_device
+    if _raw_stream is None:
+        torch = _th()
+        torch.cuda.current_stream()                          # torch's own initialisation, once
+        core = torch._C
+        if not (hasattr(core, "_cuda_getCurrentRawStream") and hasattr(core, "_cuda_getDevice")):
+            return torch.cuda.current_stream().cuda_stream
+        _cur_device = core._cuda_getDevice
+        _raw_stream = core._cuda_getCurrentRawStream         # last: another thread may be looking
+    return _raw_stream(_cur_device())
 
 
 # --- the C entry points under their own names (tensors in, nothing computed here) -------------------------
