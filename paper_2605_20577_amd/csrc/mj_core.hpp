@@ -839,32 +839,37 @@ MJ_HD void eval_placed(EvalCtx &c, const Decomp &d, uint64_t trip_c, uint64_t tr
   offer(c, y, ym, fu);
 }
 
+// the winning tile w (a suit tile) as part of this decomposition's concealed runs: in the middle or on the edge of one,
+// on the open end of one
+MJ_HD void run_ways(const Decomp &d, int w, bool &closed, bool &open_end)
+{
+  int su = suit_of(w), r = rank_of(w, su);
+  uint32_t cr = pick4(d.crun[0], d.crun[1], d.crun[2], 0u, su);
+  bool mid = r >= 1 && r <= 7 && cnt3(cr, r - 1) > 0;                 // run r-1, r, r+1
+  bool low = r <= 6 && cnt3(cr, r) > 0;                               // run r, r+1, r+2
+  bool high = r >= 2 && cnt3(cr, r - 2) > 0;                          // run r-2, r-1, r
+  bool edge = (low && r == 6) || (high && r == 2);
+  closed = mid || edge;
+  open_end = (low && r != 6) || (high && r != 2);
+}
 // All ways the winning tile can sit in this decomposition: the pair or the middle or edge of a run (both leave the sets as
-// they are and are worth 2 fu: one way), a triplet, the open end of a run.
+// they are and are worth 2 fu), a triplet (one completed by another seat's tile counts as called), the open end of a run.
+// In a step a win is evaluated by a lane or two, for which straight code is the shorter chain (65,536 games: 8.44 us per
+// step, 8.53 with the loop below); one call per kind of way, as written here, is also what leaves the compiler the best
+// step kernels (gathering the ways in a word first: 1 % more time per step on 200,000 to 2^20 games).
 // MANY: whole wavefronts evaluate hands.  The ways are then walked in a loop around ONE copy of eval_placed, which the
 // wavefront runs as often as its busiest lane needs (mostly once or twice), not once per kind of way that any of its
-// lanes has: 2^20 hands 58.0 -> 44.5 us.  In a step a win is evaluated by a lane or two, for which straight code is the
-// shorter chain (65,536 games: 8.44 us per step, 8.53 with the loop).
+// lanes has: 2^20 hands 58.0 -> 44.5 us.
 template <bool MANY>
 MJ_HD void eval_decomp(EvalCtx &c, const Decomp &d)
 {
-  enum : uint32_t { CLOSED = 1, TRIPLET = 2, OPEN_END = 4 };
   const int w = c.win;
-  uint32_t ways = d.pair == w ? CLOSED : 0u;
-  if (d.trip_c & kbit(w)) ways |= TRIPLET;
-  if (w < 27) {
-    int su = suit_of(w), r = rank_of(w, su);
-    uint32_t cr = pick4(d.crun[0], d.crun[1], d.crun[2], 0u, su);
-    bool mid = r >= 1 && r <= 7 && cnt3(cr, r - 1) > 0;                 // run r-1, r, r+1
-    bool low = r <= 6 && cnt3(cr, r) > 0;                               // run r, r+1, r+2
-    bool high = r >= 2 && cnt3(cr, r - 2) > 0;                          // run r-2, r-1, r
-    bool edge = (low && r == 6) || (high && r == 2);
-    bool two = (low && r != 6) || (high && r != 2);
-    if (mid || edge) ways |= CLOSED;
-    if (two) ways |= OPEN_END;
-  }
-  const uint64_t called = c.tsumo ? 0ull : kbit(w);      // a triplet completed by another seat's tile counts as called
-  if (MANY) {
+  bool closed = false, open_end = false;
+  if constexpr (MANY) {
+    enum : uint32_t { CLOSED = 1, TRIPLET = 2, OPEN_END = 4 };
+    if (w < 27) run_ways(d, w, closed, open_end);
+    uint32_t ways = (d.pair == w || closed ? CLOSED : 0u) | (d.trip_c & kbit(w) ? TRIPLET : 0u) | (open_end ? OPEN_END : 0u);
+    const uint64_t called = c.tsumo ? 0ull : kbit(w);
 #pragma unroll 1
     while (ways) {
       const uint32_t way = ways & (0u - ways);
@@ -873,9 +878,16 @@ MJ_HD void eval_decomp(EvalCtx &c, const Decomp &d)
       eval_placed(c, d, d.trip_c & ~moved, d.trip_o | moved, way == CLOSED ? 2 : 0, way == OPEN_END);
     }
   } else {
-    if (ways & CLOSED) eval_placed(c, d, d.trip_c, d.trip_o, 2, false);
-    if (ways & TRIPLET) eval_placed(c, d, d.trip_c & ~called, d.trip_o | called, 0, false);
-    if (ways & OPEN_END) eval_placed(c, d, d.trip_c, d.trip_o, 0, true);
+    if (d.pair == w) eval_placed(c, d, d.trip_c, d.trip_o, 2, false);
+    if (d.trip_c & kbit(w)) {
+      if (c.tsumo) eval_placed(c, d, d.trip_c, d.trip_o, 0, false);
+      else eval_placed(c, d, d.trip_c & ~kbit(w), d.trip_o | kbit(w), 0, false);
+    }
+    if (w < 27) {
+      run_ways(d, w, closed, open_end);
+      if (closed) eval_placed(c, d, d.trip_c, d.trip_o, 2, false);
+      if (open_end) eval_placed(c, d, d.trip_c, d.trip_o, 0, true);
+    }
   }
 }
 

@@ -131,12 +131,8 @@ MJ_HD void eval_seat(Ctx &c, int s, int w, bool tsumo, bool chankan, HandOut &ou
   q.seat_wind = (s - dealer_of(c)) & 3;
   q.round_wind = c.g.kyoku >> 2;
   q.n_ind = c.g.n_dora;
-  // the indicators are the wall's bytes 126..130 and 131..135, in its words 31..33; a kind is an id without its two low bits
-  const int64_t last = (int64_t)(c.g.wall_sel * 34) * c.e.n, n = c.e.n;
-  const uint32_t w31 = c.e.wallw[last + 31 * n], w32 = c.e.wallw[last + 32 * n], w33 = c.e.wallw[last + 33 * n];
-  const uint64_t ind = (uint64_t)(w31 >> 16) | (uint64_t)w32 << 16, ura = (uint64_t)(w32 >> 24) | (uint64_t)w33 << 8;
 #pragma unroll
-  for (int i = 0; i < 5; i++) { q.ind[i] = (uint8_t)(ind >> (8 * i + 2) & 63u); q.ura[i] = (uint8_t)(ura >> (8 * i + 2) & 63u); }
+  for (int i = 0; i < 5; i++) { q.ind[i] = WALL(c, 126 + i) >> 2; q.ura[i] = WALL(c, 131 + i) >> 2; }
   int aka = popc32(sw & 7u);
   for (int j = 0; j < q.n_meld; j++) aka += (int)(meld_at(q.meldw, j) >> 13 & 1u);
   if (!tsumo && !chankan && code_red(c.g.last_discard) && code_kind(c.g.last_discard) == w) aka++;

@@ -513,12 +513,15 @@ __device__ __forceinline__ uint32_t sample_actors(Ctx &c, uint64_t step, int &ro
 // s_getreg operand: hardware register HW_ID (4), bits 0..3, the wavefront's slot on its SIMD
 constexpr int kHwRegWaveSlot = 4 | 0 << 6 | (4 - 1) << 11;
 
-// n_steps of { sample, step, optional reset } without leaving the kernel: environments never interact
-__global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t B, Rules R, DevTables T, int lanes, uint64_t step0,
+// n_steps of { sample, step, optional reset } without leaving the kernel: environments never interact.
+// LANES: environments per wavefront, 0 = the run-time `lanes_arg`.  A full machine has its own instantiations because the
+// constant is worth 0.5 % there.  ONE_ROUND: the whole launch is resident at once.
+template <int LANES, bool ONE_ROUND>
+__global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t B, Rules R, DevTables T, int lanes_arg, uint64_t step0,
                                                     int n_steps, int auto_reset, int64_t env_lo, int64_t env_hi)
 {
   extern __shared__ __align__(16) uint8_t lds[];
-  BlockMem m = carve_block(T, lds, lanes);
+  BlockMem m = carve_block(T, lds, LANES ? LANES : lanes_arg);
   const int64_t b = env_lo + m.b;      // the launch covers environments [env_lo, env_hi)
   const bool active = m.lane_on && b < env_hi;
   Ctx c;
@@ -538,10 +541,12 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t
   // Two wavefronts share a SIMD and the older one (slot 0) wins every arbitration: it needs 7.7 us per step, the younger
   // one 9.1 us, and the launch ends with the younger one.  So that one is given the upper hand in every second step
   // (8.3 / 8.5 us; B = 65,536: 9.08 -> 8.54 us per step of a 512-step launch, 2,048 games 5.39 -> 4.92; in two of three or
-  // five of eight steps is no better).
-  const bool younger = __builtin_amdgcn_s_getreg(kHwRegWaveSlot) & 1;
+  // five of eight steps is no better).  Not where finished blocks are replaced: there a wavefront that is ahead only lets
+  // the next one start earlier, and the rule costs 2 to 4 % (512 steps, red rules, without / with it: 65,537 games 6.2 / 6.5
+  // ms, 200,000: 16.8 / 17.4, 400,000: 29.5 / 30.2, 2^20: 72.1 / 73.5); its code alone, switched off at run time, costs 1 %.
+  const bool younger = ONE_ROUND && (__builtin_amdgcn_s_getreg(kHwRegWaveSlot) & 1);
   for (int t = 0; t < n_steps; t++) {
-    if (younger) { if (t & 1) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0); }
+    if (ONE_ROUND && younger) { if (t & 1) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0); }
     uint32_t acts = 0;
     MJ_RB(loop, true);
     // The stride of the cold arrays is made opaque once per step: otherwise every address "array + k * stride" is
@@ -1325,7 +1330,17 @@ inline unsigned eval_blocks(int64_t n, int lanes) { const int64_t e = (int64_t)(
 // a step kernel over n_envs environments: its arguments start with (state, B, rules, tables, environments per wavefront)
 #define MJ_LAUNCH_STEP(kern, h, st, n_envs, ...)                                                                 \
   kern<<<step_blocks((n_envs), (h)->lanes), kBlock, (h)->lds_bytes, st>>>((h)->d_state, (h)->B, (h)->R, (h)->T, (h)->lanes, __VA_ARGS__)
+// environments that the step kernels hold at once: four blocks per compute unit
+inline int64_t resident_envs(int n_cu, int lanes) { return (int64_t)n_cu * 4 * envs_per_block(lanes); }
 inline int check(hipError_t e) { return e == hipSuccess ? MJ_OK : MJ_E_HIP; }
+// the fused kernel over environments [lo, hi); a batch with fewer than 32 environments per wavefront is resident at once
+int launch_rollout(const MjHandle *h, hipStream_t st, uint64_t step0, int n_steps, int auto_reset, int64_t lo, int64_t hi)
+{
+  if (h->lanes < kMaxLanes) MJ_LAUNCH_STEP((k_rollout<0, true>), h, st, hi - lo, step0, n_steps, auto_reset, lo, hi);
+  else if (hi - lo <= resident_envs(h->n_cu, kMaxLanes)) MJ_LAUNCH_STEP((k_rollout<kMaxLanes, true>), h, st, hi - lo, step0, n_steps, auto_reset, lo, hi);
+  else MJ_LAUNCH_STEP((k_rollout<kMaxLanes, false>), h, st, hi - lo, step0, n_steps, auto_reset, lo, hi);
+  return check(hipGetLastError());
+}
 
 // Three blocks fit a compute unit (LDS; smaller groups need less, but are used only where each block has one); they take
 // the groups in order from a counter, so that the blocks in flight write one compact, advancing window
@@ -1577,7 +1592,7 @@ int mj_step_random(MjHandle *h, int32_t n_steps, int auto_reset, int write_obs, 
     // over x slices' worth of games takes about x + 0.5 (x = 2 / 3 / 4: 2.6 / 3.5 / 4.3; B = 131,072: 5.3 G env
     // steps/s) and only from x = 6 on about x; sliced launches take ceil(x), however small the last slice is
     // (B = 131,072: 7.0 G).  So slices are used when the last one is more than half full.
-    const int64_t resident = (int64_t)h->n_cu * 4 * envs_per_block(h->lanes);
+    const int64_t resident = resident_envs(h->n_cu, h->lanes);
     const int64_t tail = h->B % resident;
     const bool slices = h->lanes == kMaxLanes && h->B <= 6 * resident && (tail == 0 || 2 * tail > resident);
     const int64_t per_slice = slices ? resident : h->B;
@@ -1585,14 +1600,12 @@ int mj_step_random(MjHandle *h, int32_t n_steps, int auto_reset, int write_obs, 
       int n = n_steps - t < chunk ? n_steps - t : chunk;
       for (int64_t lo = 0; lo < h->B && rc == MJ_OK; lo += per_slice) {
         const int64_t hi = lo + per_slice < h->B ? lo + per_slice : h->B;
-        MJ_LAUNCH_STEP(k_rollout, h, st, hi - lo, h->step + t, n, auto_reset, lo, hi);
-        rc = check(hipGetLastError());
+        rc = launch_rollout(h, st, h->step + t, n, auto_reset, lo, hi);
       }
     }
   } else {
     for (int t = 0; t < n_steps && rc == MJ_OK; t++) {
-      MJ_LAUNCH_STEP(k_rollout, h, st, h->B, h->step + t, 1, auto_reset, (int64_t)0, h->B);
-      rc = check(hipGetLastError());
+      rc = launch_rollout(h, st, h->step + t, 1, auto_reset, 0, h->B);
       if (rc == MJ_OK) rc = mj_observe(h, d_obs, stream);
     }
   }

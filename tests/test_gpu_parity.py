@@ -192,6 +192,21 @@ def test_games_per_wavefront(B, lanes, monkeypatch):
     assert not diff_records(o.export(), g.export())
 
 
+@pytest.mark.parametrize("B", [65536, 65537, 98304, 100001])
+def test_fused_steps_of_a_full_and_an_overfull_machine(B):
+    """256 compute units hold 65,536 games at once: launches of that size, one launch whose finished blocks are replaced
+    (65,537), slices of that size with a half-full (98,304: one launch still) and a fuller last one (100,001); the games at
+    both ends and around the end of the first slice against the oracle"""
+    kw = dict(flags=mjo.RULES_RED, mode=mjo.MODE_SINGLE)
+    g = GpuEngine(B, seed=41, **kw)
+    g.step_random(90)
+    for lo, n in {(0, 40), (min(65516, B - 40), 40), (B - 40, 40)}:
+        o = mjo.Oracle(n, 41, env_id_base=lo, **kw)
+        o.step_random(90)
+        assert not diff_records(o.export(), g.export(lo, n))
+    g.close()
+
+
 def test_full_size_sampled_envs():
     """B=65,536 in the benchmark's launch shape; sampled environments recomputed one by one by the oracle"""
     B, steps = 65536, 400
