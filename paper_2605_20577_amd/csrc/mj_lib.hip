@@ -1138,19 +1138,24 @@ template <int E> __global__ void __launch_bounds__(kAuxBlock) k_observe(void *st
 // Token observation.  One lane per (environment, seat).  What the four viewers of a game share is computed once:
 // lane (env, s) turns seat s's river into token bytes in LDS and, as viewer s, writes the first 96 bytes of its record
 // (own hand, shanten number, scalars, the seats' words rotated to it) into LDS.  The block then streams the records
-// out: a wavefront takes sixteen games, two at a time, and each half of it writes a game's four records of 31 chunks of
-// 16 bytes (6 from the record head, 8 from the four rivers picked by relative seat, 1 with the length of the history, 16
-// of history with the seats turned to the viewer), lane by lane on consecutive addresses.  The history goes from its row
-// to registers, 16 bytes per lane of one contiguous run, once for the four viewers.
+// out: a wavefront takes a quarter of the block's games, two at a time, and each half of it writes a game's four records
+// of 31 chunks of 16 bytes (6 from the record head, 8 from the four rivers picked by relative seat, 1 with the length of
+// the history, 16 of history with the seats turned to the viewer), lane by lane on consecutive addresses.  The history
+// goes from its row to registers, 16 bytes per lane of one contiguous run, once for the four viewers.
 // Bound by its stores and by the one round of loads before them (1,024 blocks of 65,536 games fit the machine at once,
 // four per compute unit; with the history in LDS only three did).  65,536 games 56.6 -> 45 to 47 us, 262,144 games 159 -> 145
 // us; the viewers' loop is rolled because code is read cold in every launch (unrolled: 48.1 us).
+// Few games are a chain of loads, one pair of games after the other, so that a block which is not full still spreads them
+// over its four wavefronts (sixteen games in one wavefront, three idle: 16.0 us; spread: 11.1; the chunks of all games
+// of a viewer in a wavefront of its own: 13.1).  VIEWER_EACH, for one or two games: a wavefront writes the records of one
+// viewer (one game 9.9 us, 10.3 with the four viewers in turn; it loses from three games on).
 constexpr int kTokEnvs = kAuxBlock / 4;           // 64 environments per block
 constexpr int kTokHead = 96;                      // bytes of MjTokenObs before river[][]
 constexpr int kTokHeadStride = 100, kTokRivStride = 36;   // LDS strides: an odd number of words, so that the lanes of a
                                                           // wavefront (consecutive environments) fall into different banks
 static_assert(offsetof(MjTokenObs, river) == kTokHead && offsetof(MjTokenObs, n_hist) == kTokHead + 128 &&
               offsetof(MjTokenObs, hist) == kTokHead + 144 && sizeof(MjTokenObs) == kTokHead + 144 + 256, "token record layout");
+template <bool VIEWER_EACH>
 __global__ void __launch_bounds__(kAuxBlock, 4) k_observe_tokens(void *state, int64_t B, uint32_t rule_flags, const uint32_t *sh_suit,
                                                               const uint32_t *sh_honor, MjTokenObs *out)
 {
@@ -1184,15 +1189,20 @@ __global__ void __launch_bounds__(kAuxBlock, 4) k_observe_tokens(void *state, in
     tok_seats(sw, sc, ml, s, o);
   }
   static_assert(sizeof(MjTokenObs) == 31 * 16 && kAuxBlock / 64 == 4 && kTokEnvs == 64, "token record chunks");
-  const int ch = tid & 31, first = 16 * (tid >> 6) + (tid >> 5 & 1);        // this lane's chunk, its half's first game
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int me0 = VIEWER_EACH ? wave : 0, me1 = VIEWER_EACH ? wave + 1 : 4;
+  // this wavefront's games: an even number, at most sixteen, from `from` on
+  const int per = 2 * ((nenv + 7) / 8), from = VIEWER_EACH ? 0 : per * wave, end = from + per < nenv ? from + per : nenv;
+  const int ch = tid & 31, first = from + (tid >> 5 & 1);                  // this lane's chunk, its half's first game
   const bool live = ch < 31, is_len = ch == 14, is_hist = ch > 14 && live;
   u32x4 hv[8];
   const uint16_t *rows = make_env(state, B, base).hist;
 #pragma unroll
   for (int it = 0; it < 8; it++) {
+    if (2 * it >= per) break;
     const int env = first + 2 * it;
     u32x4 x = {0u, 0u, 0u, 0u};
-    if (is_hist && env < nenv) {
+    if (is_hist && env < end) {
       const uint16_t *row = rows + (size_t)env * 128 + 8 * (ch - 15);
 #pragma unroll
       for (int j = 0; j < 4; j++) x[j] = row_word(row, j);
@@ -1208,8 +1218,9 @@ __global__ void __launch_bounds__(kAuxBlock, 4) k_observe_tokens(void *state, in
   u32x4 *dst = (u32x4 *)(out + base * 4) + ch;
 #pragma unroll
   for (int it = 0; it < 8; it++) {
+    if (2 * it >= per) break;
     const int env = first + 2 * it;
-    if (env < nenv) {
+    if (env < end) {
       const int nh = (int)M.nhist[env];
       u32x4 hx = hv[it];
 #pragma unroll
@@ -1218,7 +1229,7 @@ __global__ void __launch_bounds__(kAuxBlock, 4) k_observe_tokens(void *state, in
         hx[j] |= (i0 < nh ? 0u : 0xFFFFu) | (i0 + 1 < nh ? 0u : 0xFFFF0000u);
       }
 #pragma unroll 1
-      for (int me = 0; me < 4; me++) {
+      for (int me = me0; me < me1; me++) {
         const uint32_t *p = (const uint32_t *)(src + (((seat0 + me) & 3) * kTokEnvs + env) * stride);
         u32x4 v;
         v.x = p[0]; v.y = p[1]; v.z = p[2]; v.w = p[3];
@@ -1531,7 +1542,8 @@ int mj_observe_tokens(const MjHandle *h, MjTokenObs *d_out, void *stream)
 {
   if (!h || !d_out || ((uintptr_t)d_out & 15)) return MJ_E_ARG;
   const unsigned grid = (unsigned)((h->B + kTokEnvs - 1) / kTokEnvs);
-  k_observe_tokens<<<grid, kAuxBlock, 0, (hipStream_t)stream>>>(h->d_state, h->B, h->R.flags, h->sh_suit, h->sh_honor, d_out);
+  if (h->B <= 2) k_observe_tokens<true><<<grid, kAuxBlock, 0, (hipStream_t)stream>>>(h->d_state, h->B, h->R.flags, h->sh_suit, h->sh_honor, d_out);
+  else k_observe_tokens<false><<<grid, kAuxBlock, 0, (hipStream_t)stream>>>(h->d_state, h->B, h->R.flags, h->sh_suit, h->sh_honor, d_out);
   return check(hipGetLastError());
 }
 

@@ -528,10 +528,10 @@ def test_token_observation(B, flags, mode):
         assert {-1, 0, 1, 2, 3, 4, 5} <= shanten_seen
 
 
-@pytest.mark.parametrize("B", [2, 63, 64, 65, 191, 1027])
+@pytest.mark.parametrize("B", [1, 2, 3, 7, 8, 9, 16, 17, 41, 57, 63, 64, 65, 67, 191, 1027])
 def test_token_records_of_part_filled_blocks(B):
-    """blocks of 64 games, sixteen per wavefront, two at a time: batches that leave halves, wavefronts and blocks part
-    empty, with short and long histories"""
+    """blocks of 64 games, an even share of them per wavefront, two at a time (one or two games: a viewer per wavefront):
+    batches that leave halves, wavefronts and blocks part empty, with short and long histories"""
     o = mjo.Oracle(B, 29, mjo.RULES_RED, mjo.MODE_HALF)
     g = GpuEngine(B, seed=29, flags=mjo.RULES_RED, mode=mjo.MODE_HALF)
     for n in (0, 1, 37, 300):
