@@ -854,22 +854,26 @@ MJ_HD void run_ways(const Decomp &d, int w, bool &closed, bool &open_end)
 }
 // All ways the winning tile can sit in this decomposition: the pair or the middle or edge of a run (both leave the sets as
 // they are and are worth 2 fu), a triplet (one completed by another seat's tile counts as called), the open end of a run.
-// In a step a win is evaluated by a lane or two, for which straight code is the shorter chain (65,536 games: 8.44 us per
-// step, 8.53 with the loop below); one call per kind of way, as written here, is also what leaves the compiler the best
-// step kernels (gathering the ways in a word first: 1 % more time per step on 200,000 to 2^20 games).
-// MANY: whole wavefronts evaluate hands.  The ways are then walked in a loop around ONE copy of eval_placed, which the
-// wavefront runs as often as its busiest lane needs (mostly once or twice), not once per kind of way that any of its
-// lanes has: 2^20 hands 58.0 -> 44.5 us.
-template <bool MANY>
+// The form is a matter of who evaluates:
+// EVAL_BATCH: whole wavefronts of hands.  The ways are walked in a loop around ONE copy of eval_placed, which the wavefront
+//   runs as often as its busiest lane needs (mostly once or twice), not once per kind of way that any of its lanes has:
+//   2^20 hands 58.0 -> 44.5 us.
+// EVAL_STEP: a step, where a lane or two evaluate and straight code is the shorter chain (65,536 games: 8.44 us per step,
+//   8.53 with the loop).  One copy per kind of way: where a SIMD has one wavefront nothing hides the fetching of code (1,000
+//   games 5.7 us per step, 6.3 with a copy at every place).
+// EVAL_FULL: a step of a full machine whose wavefronts take turns.  A copy at every place keeps the least alive around each:
+//   65,536 games 0.6 % less time per step than EVAL_STEP (without turns 0.5 % more: 200,000 games and beyond).
+enum EvalForm { EVAL_STEP, EVAL_FULL, EVAL_BATCH };
+template <EvalForm FORM>
 MJ_HD void eval_decomp(EvalCtx &c, const Decomp &d)
 {
   const int w = c.win;
+  const uint64_t called = c.tsumo ? 0ull : kbit(w);
   bool closed = false, open_end = false;
-  if constexpr (MANY) {
+  if constexpr (FORM == EVAL_BATCH) {
     enum : uint32_t { CLOSED = 1, TRIPLET = 2, OPEN_END = 4 };
     if (w < 27) run_ways(d, w, closed, open_end);
     uint32_t ways = (d.pair == w || closed ? CLOSED : 0u) | (d.trip_c & kbit(w) ? TRIPLET : 0u) | (open_end ? OPEN_END : 0u);
-    const uint64_t called = c.tsumo ? 0ull : kbit(w);
 #pragma unroll 1
     while (ways) {
       const uint32_t way = ways & (0u - ways);
@@ -877,6 +881,11 @@ MJ_HD void eval_decomp(EvalCtx &c, const Decomp &d)
       const uint64_t moved = way == TRIPLET ? called : 0ull;
       eval_placed(c, d, d.trip_c & ~moved, d.trip_o | moved, way == CLOSED ? 2 : 0, way == OPEN_END);
     }
+  } else if constexpr (FORM == EVAL_STEP) {
+    if (d.trip_c & kbit(w)) eval_placed(c, d, d.trip_c & ~called, d.trip_o | called, 0, false);
+    if (w < 27) run_ways(d, w, closed, open_end);
+    if (d.pair == w || closed) eval_placed(c, d, d.trip_c, d.trip_o, 2, false);
+    if (open_end) eval_placed(c, d, d.trip_c, d.trip_o, 0, true);
   } else {
     if (d.pair == w) eval_placed(c, d, d.trip_c, d.trip_o, 2, false);
     if (d.trip_c & kbit(w)) {
@@ -891,7 +900,7 @@ MJ_HD void eval_decomp(EvalCtx &c, const Decomp &d)
   }
 }
 
-template <bool MANY = false>
+template <EvalForm FORM>
 MJ_HD void eval_hand(const Lut *Lp, const HandIn &q, HandOut &out)
 {
   const Lut &L = *Lp;
@@ -1027,7 +1036,7 @@ MJ_HD void eval_hand(const Lut *Lp, const HandIn &q, HandOut &out)
           add_record(d, i0 == 0 ? rec0[0] : L.recs[4 * (size_t)key[0] + i0], 0);
           add_record(d, i1 == 0 ? rec0[1] : L.recs[4 * (size_t)key[1] + i1], 1);
           add_record(d, i2 == 0 ? rec0[2] : L.recs[4 * (size_t)key[2] + i2], 2);
-          eval_decomp<MANY>(c, d);
+          eval_decomp<FORM>(c, d);
         }
     c.colour_ym &= ~gates;
   }

@@ -37,6 +37,7 @@ struct Ctx {
   bool need_turn;      // the seat to move still needs its legal mask (step_finish)
   uint32_t live_word;  // the wall word that holds the next live tile, loaded at the start of the step ...
   int live_ptr;        // ... for this draw pointer (-1: nothing loaded)
+  bool full = false;   // a kernel's constant: hands are evaluated as EVAL_FULL
 };
 
 // ------------------------------------------------------------- field access
@@ -140,7 +141,7 @@ MJ_HD void eval_seat(Ctx &c, int s, int w, bool tsumo, bool chankan, HandOut &ou
   q.n_aka = aka;
   q.kuitan = (c.R.flags & F_KUITAN) ? 1 : 0;
   MJ_RB(ev, true);
-  eval_hand(&c.L, q, out);
+  if (c.full) eval_hand<EVAL_FULL>(&c.L, q, out); else eval_hand<EVAL_STEP>(&c.L, q, out);
   MJ_RE(ev, PR_EVAL);
 }
 

@@ -515,8 +515,8 @@ constexpr int kHwRegWaveSlot = 4 | 0 << 6 | (4 - 1) << 11;
 
 // n_steps of { sample, step, optional reset } without leaving the kernel: environments never interact.
 // LANES: environments per wavefront, 0 = the run-time `lanes_arg`.  A full machine has its own instantiations because the
-// constant is worth 0.5 % there.  ONE_ROUND: the whole launch is resident at once.
-template <int LANES, bool ONE_ROUND>
+// constant is worth 0.5 % there.  TURNS: the two wavefronts of a SIMD take turns in having priority (takes_turns).
+template <int LANES, bool TURNS>
 __global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t B, Rules R, DevTables T, int lanes_arg, uint64_t step0,
                                                     int n_steps, int auto_reset, int64_t env_lo, int64_t env_hi)
 {
@@ -526,7 +526,7 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t
   const bool active = m.lane_on && b < env_hi;
   Ctx c;
   c.e = block_env(m, state, B, active ? b : 0); c.L = m.L; c.R = R; c.env_id = R.env_id_base + (uint32_t)b;
-  c.need_deal = false; c.need_turn = false; c.live_ptr = -1;
+  c.need_deal = false; c.need_turn = false; c.live_ptr = -1; c.full = LANES == kMaxLanes && TURNS;
   const TableRegs tr = table_fetch(T);
   if (active) { load_hot(m, state, B, b); load_glob(c.e, c.g); }
   table_commit(T, lds, tr);
@@ -541,12 +541,10 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t
   // Two wavefronts share a SIMD and the older one (slot 0) wins every arbitration: it needs 7.7 us per step, the younger
   // one 9.1 us, and the launch ends with the younger one.  So that one is given the upper hand in every second step
   // (8.3 / 8.5 us; B = 65,536: 9.08 -> 8.54 us per step of a 512-step launch, 2,048 games 5.39 -> 4.92; in two of three or
-  // five of eight steps is no better).  Not where finished blocks are replaced: there a wavefront that is ahead only lets
-  // the next one start earlier, and the rule costs 2 to 4 % (512 steps, red rules, without / with it: 65,537 games 6.2 / 6.5
-  // ms, 200,000: 16.8 / 17.4, 400,000: 29.5 / 30.2, 2^20: 72.1 / 73.5); its code alone, switched off at run time, costs 1 %.
-  const bool younger = ONE_ROUND && (__builtin_amdgcn_s_getreg(kHwRegWaveSlot) & 1);
+  // five of eight steps is no better).  Without TURNS the code is left out: switched off at run time it costs 1 %.
+  const bool younger = TURNS && (__builtin_amdgcn_s_getreg(kHwRegWaveSlot) & 1);
   for (int t = 0; t < n_steps; t++) {
-    if (ONE_ROUND && younger) { if (t & 1) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0); }
+    if (TURNS && younger) { if (t & 1) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0); }
     uint32_t acts = 0;
     MJ_RB(loop, true);
     // The stride of the cold arrays is made opaque once per step: otherwise every address "array + k * stride" is
@@ -927,7 +925,7 @@ __global__ void __launch_bounds__(kAuxBlock, MJ_OCC) k_eval_hands(DevTables T, i
     hi.ind[j] = (uint8_t)byte_of(offsetof(MjHandQuery, ind) + j); hi.ura[j] = (uint8_t)byte_of(offsetof(MjHandQuery, ura) + j);
   }
   HandOut ho;
-  eval_hand<true>(&L, hi, ho);
+  eval_hand<EVAL_BATCH>(&L, hi, ho);
   MjHandResult r;
   r.yaku = ho.yaku; r.points = ho.points; r.han = (uint8_t)ho.han; r.fu = (uint8_t)ho.fu;
   r.yakuman_units = (uint8_t)ho.units; r.shape_ok = (uint8_t)ho.shape_ok; r.yaku_ok = (uint8_t)ho.yaku_ok;
@@ -1344,11 +1342,24 @@ inline unsigned eval_blocks(int64_t n, int lanes) { const int64_t e = (int64_t)(
 // environments that the step kernels hold at once: four blocks per compute unit
 inline int64_t resident_envs(int n_cu, int lanes) { return (int64_t)n_cu * 4 * envs_per_block(lanes); }
 inline int check(hipError_t e) { return e == hipSuccess ? MJ_OK : MJ_E_HIP; }
+// Whether a fused launch over n environments at 32 per wavefront lets the wavefronts of a SIMD take turns.  A launch that is
+// resident at once ends with its slowest wavefront, and turns make the two alike.  In a longer one a finished block is
+// replaced, and uneven wavefronts only start the next blocks earlier; alike they end together, round by round, which pays
+// again when a last round of about half a machine then has its SIMDs to itself.  After `rounds` full rounds it does from a
+// last round of rounds / (2 rounds + 2) of the machine on, up to 7/8.  512 steps, time without / with turns over that of a
+// kernel that has none in its code, x = machines full of games: x = 1.1: 1.00 / 1.04, 1.24: 1.01 / 1.08, 1.3: 1.01 / 0.96,
+// 1.5: 1.00 / 0.97, 2.3: 1.01 / 1.02, 2.36: 1.00 / 0.97, 3.3: 1.01 / 1.02, 3.5: 1.01 / 0.98, 6.3: 1.01 / 1.02, 6.6: 1.00 /
+// 0.99, 8: 1.00 / 1.03, 16: 1.00 / 1.02.  20 steps gain and lose half as much.
+inline bool takes_turns(int64_t n, int64_t resident)
+{
+  const int64_t rounds = n / resident, tail = n % resident;
+  return n <= resident || (2 * (rounds + 1) * tail >= rounds * resident && 8 * tail <= 7 * resident);
+}
 // the fused kernel over environments [lo, hi); a batch with fewer than 32 environments per wavefront is resident at once
 int launch_rollout(const MjHandle *h, hipStream_t st, uint64_t step0, int n_steps, int auto_reset, int64_t lo, int64_t hi)
 {
   if (h->lanes < kMaxLanes) MJ_LAUNCH_STEP((k_rollout<0, true>), h, st, hi - lo, step0, n_steps, auto_reset, lo, hi);
-  else if (hi - lo <= resident_envs(h->n_cu, kMaxLanes)) MJ_LAUNCH_STEP((k_rollout<kMaxLanes, true>), h, st, hi - lo, step0, n_steps, auto_reset, lo, hi);
+  else if (takes_turns(hi - lo, resident_envs(h->n_cu, kMaxLanes))) MJ_LAUNCH_STEP((k_rollout<kMaxLanes, true>), h, st, hi - lo, step0, n_steps, auto_reset, lo, hi);
   else MJ_LAUNCH_STEP((k_rollout<kMaxLanes, false>), h, st, hi - lo, step0, n_steps, auto_reset, lo, hi);
   return check(hipGetLastError());
 }

@@ -34,6 +34,7 @@ static Ctx ctx_of(Sim *h, int64_t b)
   c.e = make_env(h->state.data(), h->B, b);
   c.L = h->L; c.R = h->R; c.env_id = h->R.env_id_base + (uint32_t)b;
   c.need_deal = false; c.need_turn = false; c.live_ptr = -1;
+  c.full = b & 1;                               // every other game evaluates its hands as on a full machine
   return c;
 }
 static void reset_env(Ctx &c, bool first)
@@ -210,7 +211,7 @@ void hs_eval_hands(Sim *h, int64_t n, const MjHandQuery *in, MjHandResult *out)
     hi.seat_wind = q.seat_wind; hi.round_wind = q.round_wind; hi.n_ind = q.n_ind; hi.n_aka = q.n_aka; hi.kuitan = q.kuitan;
     for (int j = 0; j < 5; j++) { hi.ind[j] = q.ind[j]; hi.ura[j] = q.ura[j]; }
     HandOut ho;
-    eval_hand(&h->L, hi, ho);
+    eval_hand<EVAL_STEP>(&h->L, hi, ho);
     MjHandResult r;
     memset(&r, 0, sizeof r);
     r.yaku = ho.yaku; r.points = ho.points; r.han = (uint8_t)ho.han; r.fu = (uint8_t)ho.fu;

@@ -194,9 +194,9 @@ def test_games_per_wavefront(B, lanes, monkeypatch):
 
 @pytest.mark.parametrize("B", [65536, 65537, 98304, 100001])
 def test_fused_steps_of_a_full_and_an_overfull_machine(B):
-    """256 compute units hold 65,536 games at once: launches of that size, one launch whose finished blocks are replaced
-    (65,537), slices of that size with a half-full (98,304: one launch still) and a fuller last one (100,001); the games at
-    both ends and around the end of the first slice against the oracle"""
+    """256 compute units hold 65,536 games at once: a launch of that size, longer launches whose finished blocks are replaced
+    (65,537, and 98,304 where wavefronts take turns in having priority), slices (100,001); the games at both ends and around
+    the end of the first slice against the oracle"""
     kw = dict(flags=mjo.RULES_RED, mode=mjo.MODE_SINGLE)
     g = GpuEngine(B, seed=41, **kw)
     g.step_random(90)
