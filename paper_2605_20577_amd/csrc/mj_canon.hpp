@@ -1,109 +1,204 @@
 // Conversion between the packed structure-of-arrays state and the canonical
-// per-environment record of include/mj.h, and the observation bit planes.
+// per-environment record of include/mj.h, the hand query records, and the observations.
 #pragma once
+#include <cstddef>
 #include "../../include/mj.h"
 #include "mj_engine.hpp"
 #include "mj_layout.hpp"
 
 namespace mj {
 
-MJ_HD void export_env(const Env &e, MjEnvCanon &o)
+// ------------------------------------------------------------------- records
+// A canonical record is 250 words.  It is written and read in eight parts, so that the kernels can give each part of a
+// group of games to a wavefront of its own; what a part holds is fixed here, once, for the kernels and for export_env /
+// import_env, which go through the parts one after the other.  All loads of a part are issued before its stores.
+constexpr int kRecParts = 8;
+constexpr int kRecWords = (int)(sizeof(MjEnvCanon) / 4);
+constexpr int kRecMeld = offsetof(MjEnvCanon, meld) / 4, kRecHist = offsetof(MjEnvCanon, hist) / 4, kRecWall = offsetof(MjEnvCanon, wall) / 4,
+              kRecHand = offsetof(MjEnvCanon, hand), kRecRiver = offsetof(MjEnvCanon, river), kRecSeat = offsetof(MjEnvCanon, hand_red),
+              kRecResult = offsetof(MjEnvCanon, han), kRecGlob = offsetof(MjEnvCanon, kyoku) / 4;
+static_assert(offsetof(MjEnvCanon, waits) == 32 && offsetof(MjEnvCanon, mask) == 64 && offsetof(MjEnvCanon, yaku) == 128 &&
+              offsetof(MjEnvCanon, score) == 160 && offsetof(MjEnvCanon, delta) == 176 && offsetof(MjEnvCanon, gain) == 192 &&
+              offsetof(MjEnvCanon, episode) == 208 && offsetof(MjEnvCanon, kyoku_serial) == 212 && kRecMeld == 54 && kRecHist == 62 &&
+              kRecWall == 126 && kRecSeat + 44 == kRecResult && kRecResult + 24 == 4 * kRecGlob && kRecGlob + 7 == kRecWords &&
+              offsetof(MjEnvCanon, n_hist) == 999 && offsetof(MjEnvCanon, dora_pending) == 998, "record layout in words");
+// array of the state behind row r of the record's leading 8-byte fields: discarded_kinds, waits, mask (arrays 0..15), yaku
+MJ_HD int rec_u64_array(int r) { return r < 16 ? r : kHotU64 + (r - 16); }
+// ... and behind row r of its 4-byte fields: score, delta (arrays 0..7), gain, episode, serial
+MJ_HD int rec_u32_array(int r) { return r < 8 ? r : r < 12 ? kHotU32 + (r - 8) : r - 4; }
+
+// part g of the record of a game whose every field is in HBM (make_env); the history is apart (record_hist_out)
+MJ_HD void record_part_out(const Env &e, int g, uint32_t *rec)
 {
-  Glob g;
-  load_glob(e, g);
+  uint8_t *const bytes = (uint8_t *)rec;
   const int64_t n = e.n;
-  for (int s = 0; s < 4; s++) {
-    uint32_t sw = e.seatw[s * n];
-    o.discarded_kinds[s] = e.dk[s * n];
-    o.waits[s] = e.waits[s * n] & K_ALL;                    // without the facts that ride in the upper bits
-    o.mask[s][0] = e.mask[(2 * s) * n]; o.mask[s][1] = e.mask[(2 * s + 1) * n];
-    o.yaku[s] = e.yaku[s * n];
-    o.score[s] = e.score[s * n]; o.delta[s] = e.delta[s * n]; o.gain[s] = e.gain[s * n];
-    uint64_t mw = e.meld[s * n], rw = e.resw[s * n];
-    for (int j = 0; j < 4; j++) o.meld[s][j] = (uint16_t)(mw >> (16 * j));
-    for (int su = 0; su < 4; su++) {
-      uint32_t hw = e.hand[(s * 4 + su) * n];
-      int nr = su == 3 ? 7 : 9;
-      for (int r = 0; r < nr; r++) o.hand[s][(su == 3 ? 27 : 9 * su) + r] = (uint8_t)cnt3(hw, r);
-    }
-    int nriv = (int)sw_get(sw, SW_NRIVER, 6);
-    for (int i = 0; i < 32; i++) o.river[s][i] = i < nriv ? e.river[(s * 32 + i) * n] : 0;
-    o.hand_red[s] = (uint8_t)sw_get(sw, SW_RED, 3);
-    o.n_meld[s] = (uint8_t)sw_get(sw, SW_NMELD, 3);
-    o.n_river[s] = (uint8_t)nriv;
-    o.riichi_idx[s] = (uint8_t)sw_get(sw, SW_RIDX, 8);
-    o.riichi[s] = (uint8_t)sw_get(sw, SW_RIICHI, 2);
-    o.ippatsu[s] = (uint8_t)sw_get(sw, SW_IPPATSU, 1);
-    o.first_turn[s] = (uint8_t)sw_get(sw, SW_FIRST, 1);
-    o.furiten_temp[s] = (uint8_t)sw_get(sw, SW_FTEMP, 1);
-    o.furiten_riichi[s] = (uint8_t)sw_get(sw, SW_FRIICHI, 1);
-    o.kan_by[s] = (uint8_t)sw_get(sw, SW_KANBY, 3);
-    o.final_rank[s] = (uint8_t)sw_get(sw, SW_RANK, 2);
-    o.han[s] = (uint8_t)rw; o.fu[s] = (uint8_t)(rw >> 8); o.yakuman_units[s] = (uint8_t)(rw >> 16);
-    o.r_dora[s] = (uint8_t)(rw >> 24); o.r_ura[s] = (uint8_t)(rw >> 32); o.r_aka[s] = (uint8_t)(rw >> 40);
+  const uint32_t last = e.glob[6 * n];                                   // ... wall_sel, hist_len
+  const int s = g & 3;
+  const uint32_t sw = e.seatw[s * n];
+  const int nriv = (int)sw_get(sw, SW_NRIVER, 6);
+  const uint64_t *q = e.dk;                                              // array 0, this game
+  const uint32_t *w = (const uint32_t *)e.score;
+  uint64_t v64[3];
+  uint32_t v32[2], wall[5], hw[2], riv[16], gl = 0;
+#pragma unroll
+  for (int k = 0; k < 3; k++) { const int r = g + kRecParts * k; v64[k] = r < 20 ? q[(int64_t)rec_u64_array(r) * n] : 0ull; }
+#pragma unroll
+  for (int k = 0; k < 2; k++) { const int r = g + kRecParts * k; v32[k] = r < 14 ? w[(int64_t)rec_u32_array(r) * n] : 0u; }
+  const uint64_t seat64 = g < 4 ? e.meld[s * n] : e.resw[s * n];
+#pragma unroll
+  for (int k = 0; k < 2; k++) hw[k] = e.hand[(int64_t)(s * 4 + 2 * (g >> 2) + k) * n];
+  if (g < 7) gl = e.glob[g * n];
+  const uint32_t gl3 = e.glob[3 * n];
+#pragma unroll
+  for (int k = 0; k < 16; k++) riv[k] = e.river[(int64_t)(s * 32 + 16 * (g >> 2) + k) * n];
+  const uint32_t *wl = e.wallw + (int64_t)((last >> 16 & 1u) * 34) * n;
+#pragma unroll
+  for (int k = 0; k < 5; k++) { const int r = g + kRecParts * k; wall[k] = r < 34 ? wl[(int64_t)r * n] : 0u; }
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    const int r = g + kRecParts * k;
+    if (r >= 4 && r < 8) v64[k] &= K_ALL;                                // waits without the facts that ride in the upper bits
+    if (r < 20) { rec[2 * r] = (uint32_t)v64[k]; rec[2 * r + 1] = (uint32_t)(v64[k] >> 32); }
   }
-  o.episode = e.episode[0]; o.kyoku_serial = e.serial[0];
-  for (int i = 0; i < 136; i++) o.wall[i] = (uint8_t)wall_at(e, g.wall_sel, i);
-  o.kyoku = g.kyoku; o.honba = g.honba; o.kyotaku = g.kyotaku; o.terminated = g.terminated;
-  o.draw_ptr = g.draw_ptr; o.n_kan = g.n_kan; o.live_left = g.live_left; o.n_dora = g.n_dora;
-  o.drawn = g.drawn; o.phase = g.phase; o.cur = g.cur; o.actor_mask = g.actor_mask;
-  o.riichi_pending = g.riichi_pending; o.rinshan = g.kanflags & 1; o.last_discard = g.last_discard;
-  o.last_discarder = g.last_discarder; o.kakan_tile = g.kakan_tile; o.kuikae[0] = g.kuikae0; o.kuikae[1] = g.kuikae1;
-  o.first_wind = g.first_wind; o.same_wind_cnt = g.same_wind_cnt; o.illegal_seat = g.illegal_seat;
-  o.end_type = g.end_type; o.winners = g.winners; o.loser = g.loser; o.tenpai_mask = g.tenpai_mask;
-  o.dora_pending = g.kanflags >> 1 & 1; o.n_hist = g.hist_len;
-  for (int i = 0; i < 128; i++)
-    o.hist[i] = i < g.hist_len ? e.hist[i] : (uint16_t)0;
+#pragma unroll
+  for (int k = 0; k < 2; k++) { const int r = g + kRecParts * k; if (r < 14) rec[40 + r] = v32[k]; }
+#pragma unroll
+  for (int k = 0; k < 5; k++) { const int r = g + kRecParts * k; if (r < 34) rec[kRecWall + r] = wall[k]; }
+  if (g < 4) {
+    rec[kRecMeld + 2 * s] = (uint32_t)seat64; rec[kRecMeld + 2 * s + 1] = (uint32_t)(seat64 >> 32);
+    uint8_t *b = bytes + kRecSeat + s;
+    b[0] = (uint8_t)sw_get(sw, SW_RED, 3); b[4] = (uint8_t)sw_get(sw, SW_NMELD, 3); b[8] = (uint8_t)nriv;
+    b[12] = (uint8_t)sw_get(sw, SW_RIDX, 8); b[16] = (uint8_t)sw_get(sw, SW_RIICHI, 2); b[20] = (uint8_t)sw_get(sw, SW_IPPATSU, 1);
+    b[24] = (uint8_t)sw_get(sw, SW_FIRST, 1); b[28] = (uint8_t)sw_get(sw, SW_FTEMP, 1); b[32] = (uint8_t)sw_get(sw, SW_FRIICHI, 1);
+    b[36] = (uint8_t)sw_get(sw, SW_KANBY, 3); b[40] = (uint8_t)sw_get(sw, SW_RANK, 2);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 6; j++) bytes[kRecResult + 4 * j + s] = (uint8_t)(seat64 >> (8 * j));
+  }
+  if (g < 7) {
+    if (g == 3) gl = (gl & ~0xFE00u);                                    // kanflags: only "replacement tile" here ...
+    if (g == 6) gl = (gl & 0xFF00FFFFu) | (gl3 >> 9 & 1u) << 16;         // ... and the waiting indicator in wall_sel's place
+    rec[kRecGlob + g] = gl;
+  }
+  uint8_t *hb = bytes + kRecHand + 34 * s + 18 * (g >> 2);
+#pragma unroll
+  for (int r = 0; r < 18; r++) if (r < 16 || g < 4) hb[r] = (uint8_t)cnt3(hw[r / 9], r % 9);
+  uint8_t *rb = bytes + kRecRiver + 32 * s + 16 * (g >> 2);
+#pragma unroll
+  for (int k = 0; k < 16; k++) rb[k] = 16 * (g >> 2) + k < nriv ? (uint8_t)riv[k] : (uint8_t)0;
+}
+// word i (entries 2 i and 2 i + 1) of the record's history
+MJ_HD uint32_t record_hist_out(const Env &e, int i)
+{
+  const int nh = (int)(e.glob[6 * e.n] >> 24);
+  const uint32_t x = row_word(e.hist, i);
+  return (2 * i < nh ? x & 0xFFFFu : 0u) | (2 * i + 1 < nh ? x & 0xFFFF0000u : 0u);
 }
 
+MJ_HD void record_part_in(const Env &e, int g, const uint32_t *rec)
+{
+  const uint8_t *const bytes = (const uint8_t *)rec;
+  const int64_t n = e.n;
+  const int s = g & 3;
+  uint64_t *q = e.dk;
+  uint32_t *w = (uint32_t *)e.score;
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    const int r = g + kRecParts * k;
+    if (r < 20) q[(int64_t)rec_u64_array(r) * n] = (uint64_t)rec[2 * r] | (uint64_t)rec[2 * r + 1] << 32;
+  }
+#pragma unroll
+  for (int k = 0; k < 2; k++) { const int r = g + kRecParts * k; if (r < 14) w[(int64_t)rec_u32_array(r) * n] = rec[40 + r]; }
+#pragma unroll
+  for (int k = 0; k < 5; k++) { const int r = g + kRecParts * k; if (r < 34) e.wallw[(int64_t)r * n] = rec[kRecWall + r]; }      // buffer 0
+  if (g < 4) {
+    e.meld[s * n] = (uint64_t)rec[kRecMeld + 2 * s] | (uint64_t)rec[kRecMeld + 2 * s + 1] << 32;
+    const uint8_t *b = bytes + kRecSeat + s;
+    uint32_t sw = 0;
+    sw = sw_set(sw, SW_RED, 3, b[0] & 7u); sw = sw_set(sw, SW_NMELD, 3, b[4] & 7u); sw = sw_set(sw, SW_NRIVER, 6, b[8] & 63u);
+    sw = sw_set(sw, SW_RIDX, 8, b[12]); sw = sw_set(sw, SW_RIICHI, 2, b[16] & 3u); sw = sw_set(sw, SW_IPPATSU, 1, b[20] & 1u);
+    sw = sw_set(sw, SW_FIRST, 1, b[24] & 1u); sw = sw_set(sw, SW_FTEMP, 1, b[28] & 1u); sw = sw_set(sw, SW_FRIICHI, 1, b[32] & 1u);
+    sw = sw_set(sw, SW_KANBY, 3, b[36] & 7u); sw = sw_set(sw, SW_RANK, 2, b[40] & 3u);
+    e.seatw[s * n] = sw;
+  } else {
+    uint64_t rw = 0;
+#pragma unroll
+    for (int j = 0; j < 6; j++) rw |= (uint64_t)bytes[kRecResult + 4 * j + s] << (8 * j);
+    e.resw[s * n] = rw;
+  }
+  if (g < 7) {
+    uint32_t gl = rec[kRecGlob + g];
+    if (g == 3) gl = (gl & ~0xFF00u) | (gl >> 8 & 1u) << 8 | (rec[kRecGlob + 6] >> 16 & 1u) << 9;
+    if (g == 6) { const uint32_t nh = gl >> 24; gl = (gl & 0xFFFFu) | (nh > 128u ? 128u : nh) << 24; }      // wall_sel 0
+    e.glob[g * n] = gl;
+  } else {
+    e.nserial[0] = 0xFFFFFFFFu;                      // whatever was made ahead of time is gone
+    e.tdisc[0] = 0;                                  // ... and so is the cache of tenpai-keeping discards
+  }
+  const uint8_t *hb = bytes + kRecHand + 34 * s + 18 * (g >> 2);
+  uint32_t hw[2] = {0, 0};
+#pragma unroll
+  for (int r = 0; r < 18; r++) if (r < 16 || g < 4) hw[r / 9] |= (uint32_t)(hb[r] & 7) << (3 * (r % 9));
+#pragma unroll
+  for (int k = 0; k < 2; k++) e.hand[(int64_t)(s * 4 + 2 * (g >> 2) + k) * n] = hw[k];
+  const uint8_t *rb = bytes + kRecRiver + 32 * s + 16 * (g >> 2);
+#pragma unroll
+  for (int k = 0; k < 16; k++) e.river[(int64_t)(s * 32 + 16 * (g >> 2) + k) * n] = rb[k];
+}
+MJ_HD void record_hist_in(const Env &e, int i, uint32_t word) { set_row_word(e.hist, i, word); }
+
+MJ_HD void export_env(const Env &e, MjEnvCanon &o)
+{
+  uint32_t rec[kRecWords];
+  for (int g = 0; g < kRecParts; g++) record_part_out(e, g, rec);
+  for (int i = 0; i < 64; i++) rec[kRecHist + i] = record_hist_out(e, i);
+  __builtin_memcpy(&o, rec, sizeof o);
+}
 MJ_HD void import_env(const Env &e, const MjEnvCanon &o)
 {
-  Glob g;
-  const int64_t n = e.n;
-  for (int s = 0; s < 4; s++) {
-    e.dk[s * n] = o.discarded_kinds[s];
-    e.waits[s * n] = o.waits[s];
-    e.mask[(2 * s) * n] = o.mask[s][0]; e.mask[(2 * s + 1) * n] = o.mask[s][1];
-    e.yaku[s * n] = o.yaku[s];
-    e.score[s * n] = o.score[s]; e.delta[s * n] = o.delta[s]; e.gain[s * n] = o.gain[s];
-    uint64_t mw = 0;
-    for (int j = 0; j < 4; j++) mw |= (uint64_t)o.meld[s][j] << (16 * j);
-    e.meld[s * n] = mw;
-    e.resw[s * n] = (uint64_t)o.han[s] | (uint64_t)o.fu[s] << 8 | (uint64_t)o.yakuman_units[s] << 16 |
-                    (uint64_t)o.r_dora[s] << 24 | (uint64_t)o.r_ura[s] << 32 | (uint64_t)o.r_aka[s] << 40;
-    for (int su = 0; su < 4; su++) {
-      uint32_t hw = 0;
-      int nr = su == 3 ? 7 : 9;
-      for (int r = 0; r < nr; r++) hw |= (uint32_t)(o.hand[s][(su == 3 ? 27 : 9 * su) + r] & 7) << (3 * r);
-      e.hand[(s * 4 + su) * n] = hw;
+  uint32_t rec[kRecWords];
+  __builtin_memcpy(rec, &o, sizeof o);
+  for (int g = 0; g < kRecParts; g++) record_part_in(e, g, rec);
+  for (int i = 0; i < 64; i++) record_hist_in(e, i, rec[kRecHist + i]);
+}
+
+// -------------------------------------------------------------- hand queries
+// a query record as sixteen words, which stay in registers: every byte is read at a constant place
+MJ_HD void read_query(const uint32_t w[16], HandIn &hi)
+{
+  static_assert(sizeof(MjHandQuery) == 64 && offsetof(MjHandQuery, meld) % 2 == 0 && sizeof(MjHandQuery::meld) == 8 &&
+                sizeof(MjHandQuery::hand) == 34, "query record layout");
+#define MJ_Q(at) (w[(at) >> 2] >> (8 * ((at) & 3)) & 255u)
+#define MJ_QF(field) (int)MJ_Q(offsetof(MjHandQuery, field))
+#pragma unroll
+  for (int su = 0; su < 4; su++) {
+    uint32_t hw = 0;
+#pragma unroll
+    for (int r = 0; r < (su == 3 ? 7 : 9); r++) {
+      const uint32_t cnt = MJ_Q(offsetof(MjHandQuery, hand) + 9 * su + r);
+      hw |= (cnt > 7 ? 7u : cnt) << (3 * r);
     }
-    for (int i = 0; i < 32; i++) e.river[(s * 32 + i) * n] = o.river[s][i];
-    uint32_t sw = 0;
-    sw = sw_set(sw, SW_RED, 3, o.hand_red[s] & 7); sw = sw_set(sw, SW_NMELD, 3, o.n_meld[s] & 7);
-    sw = sw_set(sw, SW_NRIVER, 6, o.n_river[s] & 63); sw = sw_set(sw, SW_RIDX, 8, o.riichi_idx[s]);
-    sw = sw_set(sw, SW_RIICHI, 2, o.riichi[s] & 3); sw = sw_set(sw, SW_IPPATSU, 1, o.ippatsu[s] & 1);
-    sw = sw_set(sw, SW_FIRST, 1, o.first_turn[s] & 1); sw = sw_set(sw, SW_FTEMP, 1, o.furiten_temp[s] & 1);
-    sw = sw_set(sw, SW_FRIICHI, 1, o.furiten_riichi[s] & 1); sw = sw_set(sw, SW_KANBY, 3, o.kan_by[s] & 7);
-    sw = sw_set(sw, SW_RANK, 2, o.final_rank[s] & 3);
-    e.seatw[s * n] = sw;
+    hi.h[su] = hw;
   }
-  e.episode[0] = o.episode; e.serial[0] = o.kyoku_serial;
-  e.nserial[0] = 0xFFFFFFFFu;                      // whatever was made ahead of time is gone
-  e.tdisc[0] = 0;                                  // ... and so is the cache of tenpai-keeping discards
-  for (int i = 0; i < 34; i++)
-    e.wallw[i * n] = (uint32_t)o.wall[4 * i] | (uint32_t)o.wall[4 * i + 1] << 8 | (uint32_t)o.wall[4 * i + 2] << 16 |
-                     (uint32_t)o.wall[4 * i + 3] << 24;
-  g.kyoku = o.kyoku; g.honba = o.honba; g.kyotaku = o.kyotaku; g.terminated = o.terminated;
-  g.draw_ptr = o.draw_ptr; g.n_kan = o.n_kan; g.live_left = o.live_left; g.n_dora = o.n_dora;
-  g.drawn = o.drawn; g.phase = o.phase; g.cur = o.cur; g.actor_mask = o.actor_mask;
-  g.riichi_pending = o.riichi_pending; g.kanflags = (uint8_t)((o.rinshan & 1) | (o.dora_pending & 1) << 1); g.last_discard = o.last_discard;
-  g.last_discarder = o.last_discarder; g.kakan_tile = o.kakan_tile; g.kuikae0 = o.kuikae[0]; g.kuikae1 = o.kuikae[1];
-  g.first_wind = o.first_wind; g.same_wind_cnt = o.same_wind_cnt; g.illegal_seat = o.illegal_seat;
-  g.end_type = o.end_type; g.winners = o.winners; g.loser = o.loser; g.tenpai_mask = o.tenpai_mask;
-  g.wall_sel = 0;                      // the imported wall goes to buffer 0
-  g.hist_len = o.n_hist > 128 ? 128 : o.n_hist;
-  for (int i = 0; i < 128; i++) e.hist[i] = o.hist[i];
-  store_glob(e, g);
+  hi.meldw = 0;
+#pragma unroll
+  for (int j = 0; j < 8; j++) hi.meldw |= (uint64_t)MJ_Q(offsetof(MjHandQuery, meld) + j) << (8 * j);
+  hi.n_meld = MJ_QF(n_meld); hi.win = MJ_QF(win_kind); hi.flags = MJ_QF(flags); hi.riichi = MJ_QF(riichi);
+  hi.seat_wind = MJ_QF(seat_wind); hi.round_wind = MJ_QF(round_wind); hi.n_ind = MJ_QF(n_ind); hi.n_aka = MJ_QF(n_aka);
+  hi.kuitan = MJ_QF(kuitan);
+#pragma unroll
+  for (int j = 0; j < 5; j++) {
+    hi.ind[j] = (uint8_t)MJ_Q(offsetof(MjHandQuery, ind) + j); hi.ura[j] = (uint8_t)MJ_Q(offsetof(MjHandQuery, ura) + j);
+  }
+#undef MJ_QF
+#undef MJ_Q
+}
+MJ_HD void hand_result(const HandOut &ho, MjHandResult &r)
+{
+  r.yaku = ho.yaku; r.points = ho.points; r.han = (uint8_t)ho.han; r.fu = (uint8_t)ho.fu;
+  r.yakuman_units = (uint8_t)ho.units; r.shape_ok = (uint8_t)ho.shape_ok; r.yaku_ok = (uint8_t)ho.yaku_ok;
+  r.n_dora = (uint8_t)ho.n_dora; r.n_ura = (uint8_t)ho.n_ura; r.n_aka = (uint8_t)ho.n_aka;
+  r.pad_[0] = r.pad_[1] = r.pad_[2] = r.pad_[3] = 0;
 }
 
 // ---------------------------------------------------------------- observation

@@ -177,6 +177,7 @@ MJ_HD uint32_t row_word(const void *row, int i)
   __builtin_memcpy(&w, __builtin_assume_aligned((const uint8_t *)row + 4 * i, 4), 4);      // one 4-byte load
   return w;
 }
+MJ_HD void set_row_word(void *row, int i, uint32_t w) { __builtin_memcpy(__builtin_assume_aligned((uint8_t *)row + 4 * i, 4), &w, 4); }
 
 MJ_HD int m_type(uint32_t m) { return (int)(m & 7); }
 MJ_HD int m_kind(uint32_t m) { return (int)((m >> 3) & 63); }

@@ -192,31 +192,20 @@ int hs_shanten(Sim *h, const uint8_t *hand, int n_meld)
   for (int k = 0; k < 34; k++) { int su = suit_of(k); hw[su] |= (uint32_t)hand[k] << (3 * rank_of(k, su)); }
   return shanten_of(sh_suit.data(), sh_honor.data(), hw[0], hw[1], hw[2], hw[3], n_meld);
 }
-void hs_eval_hands(Sim *h, int64_t n, const MjHandQuery *in, MjHandResult *out)
+// form: EVAL_BATCH is that of k_eval_hands
+void hs_eval_hands(Sim *h, int64_t n, const MjHandQuery *in, MjHandResult *out, int form)
 {
   for (int64_t i = 0; i < n; i++) {
-    const MjHandQuery &q = in[i];
+    uint32_t w[16];
+    memcpy(w, in + i, sizeof w);
     HandIn hi;
-    for (int su = 0; su < 4; su++) {
-      uint32_t hw = 0;
-      int nr = su == 3 ? 7 : 9;
-      for (int r = 0; r < nr; r++) {
-        uint32_t cnt = q.hand[(su == 3 ? 27 : 9 * su) + r];
-        hw |= (cnt > 7 ? 7u : cnt) << (3 * r);
-      }
-      hi.h[su] = hw;
-    }
-    hi.meldw = (uint64_t)q.meld[0] | (uint64_t)q.meld[1] << 16 | (uint64_t)q.meld[2] << 32 | (uint64_t)q.meld[3] << 48;
-    hi.n_meld = q.n_meld; hi.win = q.win_kind; hi.flags = q.flags; hi.riichi = q.riichi;
-    hi.seat_wind = q.seat_wind; hi.round_wind = q.round_wind; hi.n_ind = q.n_ind; hi.n_aka = q.n_aka; hi.kuitan = q.kuitan;
-    for (int j = 0; j < 5; j++) { hi.ind[j] = q.ind[j]; hi.ura[j] = q.ura[j]; }
+    read_query(w, hi);
     HandOut ho;
-    eval_hand<EVAL_STEP>(&h->L, hi, ho);
+    if (form == EVAL_BATCH) eval_hand<EVAL_BATCH>(&h->L, hi, ho);
+    else if (form == EVAL_FULL) eval_hand<EVAL_FULL>(&h->L, hi, ho);
+    else eval_hand<EVAL_STEP>(&h->L, hi, ho);
     MjHandResult r;
-    memset(&r, 0, sizeof r);
-    r.yaku = ho.yaku; r.points = ho.points; r.han = (uint8_t)ho.han; r.fu = (uint8_t)ho.fu;
-    r.yakuman_units = (uint8_t)ho.units; r.shape_ok = (uint8_t)ho.shape_ok; r.yaku_ok = (uint8_t)ho.yaku_ok;
-    r.n_dora = (uint8_t)ho.n_dora; r.n_ura = (uint8_t)ho.n_ura; r.n_aka = (uint8_t)ho.n_aka;
+    hand_result(ho, r);
     out[i] = r;
   }
 }

@@ -26,6 +26,7 @@ def build(force=False):
 
 
 _lib = None
+EVAL_STEP, EVAL_FULL, EVAL_BATCH = 0, 1, 2
 
 
 def lib():
@@ -49,7 +50,7 @@ def lib():
         L.hs_shanten.argtypes = [vp, vp, C.c_int]
         L.hs_shanten.restype = C.c_int
         L.hs_deal_from_wall.argtypes = [vp, C.c_int64, vp]
-        L.hs_eval_hands.argtypes = [vp, C.c_int64, vp, vp]
+        L.hs_eval_hands.argtypes = [vp, C.c_int64, vp, vp, C.c_int]
         L.hs_waits.argtypes = [vp, vp, vp, C.c_int]
         L.hs_waits.restype = C.c_uint64
         L.hs_tenpai_discards.argtypes = [vp, vp, vp, C.c_int]
@@ -121,10 +122,11 @@ class HostSim:
         lib().hs_observe(self._h, _p(o))
         return o
 
-    def eval_hands(self, queries):
+    def eval_hands(self, queries, form=EVAL_BATCH):
+        """form: as the batch evaluator's kernel does it, as a step does, as a step of a full machine does"""
         q = np.ascontiguousarray(queries, dtype=QUERY_DTYPE)
         r = np.zeros(q.shape, dtype=RESULT_DTYPE)
-        lib().hs_eval_hands(self._h, q.size, _p(q), _p(r))
+        lib().hs_eval_hands(self._h, q.size, _p(q), _p(r), form)
         return r
 
     def observe_tokens(self):

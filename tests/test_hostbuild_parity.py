@@ -8,6 +8,7 @@ import pytest
 
 from oracle import mjo
 from tests.engines import diff_records
+from tests.hostsim import sim
 from tests.hostsim.sim import HostSim
 from workloads import hands
 
@@ -17,11 +18,45 @@ def test_table_counts():
     assert (keys, recs) == (21743, 23533) and rows == 98        # 97 distinct rows + the empty one
 
 
-def test_hand_microbatch():
+@pytest.mark.parametrize("form", [sim.EVAL_STEP, sim.EVAL_FULL, sim.EVAL_BATCH])
+def test_hand_microbatch(form):
+    """the three forms of the evaluator: the straight code of a step, that of a full machine's, the batch kernel's loop"""
     q = hands.generate(1 << 15, mjo.QUERY_DTYPE, seed=3)
-    ro, rh = mjo.eval_hands(q), HostSim(1).eval_hands(q)
+    ro, rh = mjo.eval_hands(q), HostSim(1).eval_hands(q, form)
     assert ro.tobytes() == rh.tobytes()
     assert ro["yaku_ok"].sum() > 5000
+
+
+def test_records_out_and_in():
+    """the record code of the export and import kernels: records of one batch into another of an odd size, and fields that an
+    import masks or clamps"""
+    kw = dict(flags=mjo.RULES_RED | mjo.F_KANDORA_LATE, mode=mjo.MODE_HALF)
+    o, s, other = mjo.Oracle(67, 19, **kw), HostSim(67, 19, **kw), mjo.Oracle(67, 20, **kw)
+    o.step_random(700); s.step_random(700); other.step_random(650)
+    f = other.export()
+    want = o.export()
+    want[7:60] = f[7:60]
+    s.import_(f[7:60], 7)
+    assert not diff_records(want, s.export())
+    s = HostSim(67, 20, **kw)
+    s.import_(f)
+    other.import_(f)
+    for _ in range(60):                        # both go on from the records, step by step: deals, wins, late indicators
+        a = other.sample_random()
+        other.step(a); s.step(a)
+        assert not diff_records(other.export(), s.export())
+    raw = f.copy()
+    bits = ("ippatsu", "first_turn", "furiten_temp", "furiten_riichi", "rinshan", "dora_pending")
+    for name in bits:
+        raw[name] |= 0xFE
+    for name, mask in (("hand_red", 7), ("n_meld", 7), ("riichi", 3), ("kan_by", 7), ("final_rank", 3)):
+        raw[name] |= 255 ^ mask
+    raw["n_hist"] = 200
+    s.import_(raw)
+    got = s.export()
+    assert np.array_equal(got["n_hist"], np.full(67, 128)) and np.array_equal(got["hist"], raw["hist"])
+    for name in bits + ("hand_red", "n_meld", "riichi", "kan_by", "final_rank"):
+        assert np.array_equal(got[name], f[name]), name
 
 
 @pytest.mark.parametrize("flags,mode,steps", [(mjo.RULES_NORED, mjo.MODE_SINGLE, 160), (mjo.RULES_RED, mjo.MODE_HALF, 1200),
