@@ -46,6 +46,29 @@ def test_binding_refuses_to_run_without_the_library(monkeypatch):
         b.lib()
 
 
+@pytest.mark.parametrize("raw", [True, False])
+def test_binding_stream_handle(raw, monkeypatch):
+    """the launches' stream is the current device's current one at every call, through torch's raw handle where this torch
+    has it and through its Stream object where not"""
+    import types
+    import paper_2605_20577_amd.binding as b
+    now = {"device": 0, "stream": {0: 0x1000, 1: 0x2000}}
+    handle = lambda device: now["stream"][device]
+    core = types.SimpleNamespace(_cuda_getDevice=lambda: now["device"])
+    if raw:
+        core._cuda_getCurrentRawStream = handle
+    cuda = types.SimpleNamespace(current_stream=lambda: types.SimpleNamespace(cuda_stream=handle(now["device"])))
+    monkeypatch.setattr(b, "_torch", types.SimpleNamespace(cuda=cuda, _C=core))
+    monkeypatch.setattr(b, "_raw_stream", None)
+    monkeypatch.setattr(b, "_cur_device", None)
+    assert b._stream() == 0x1000
+    now["stream"][0] = 0x3000
+    assert b._stream() == 0x3000
+    now["device"] = 1
+    assert b._stream() == 0x2000
+    assert (b._raw_stream is not None) == raw
+
+
 def test_binding_constants_mirror_the_header():
     import re
     import paper_2605_20577_amd as mj

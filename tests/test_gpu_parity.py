@@ -433,6 +433,45 @@ def test_hands_per_wavefront(n):
     g.close()
 
 
+def test_calls_go_to_the_current_stream():
+    """every call is enqueued on torch's current stream: the handle follows torch.cuda.stream blocks, and a whole step made
+    on a stream of its own is complete when that stream alone is waited for"""
+    import torch
+    from paper_2605_20577_amd import binding
+    B = 3000
+    o = mjo.Oracle(B, 43, mjo.RULES_RED, mjo.MODE_HALF)
+    g = GpuEngine(B, seed=43, flags=mjo.RULES_RED, mode=mjo.MODE_HALF)
+    torch.cuda.synchronize()
+    outside = torch.cuda.current_stream().cuda_stream
+    assert binding._stream() == outside
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    assert streams[0].cuda_stream != streams[1].cuda_stream
+    for i, s in enumerate(streams):
+        with torch.cuda.stream(s):
+            assert binding._stream() == s.cuda_stream != outside
+            g.env.step_random(30)
+            a = g.env.sample_random()
+            mask, delta, reward, term = g.env.step_full(a)
+            tokens = g.env.observe_tokens()
+            host = [torch.empty(t.shape, dtype=t.dtype, pin_memory=True) for t in (a, mask, delta, term, tokens)]
+            for h, t in zip(host, (a, mask, delta, term, tokens)):
+                h.copy_(t, non_blocking=True)
+        assert binding._stream() == outside
+        s.synchronize()
+        o.step_random(30)
+        want = o.sample_random()
+        o.step(want)
+        od, _, ot = o.reward()
+        o.reset_done()
+        assert np.array_equal(want, host[0].numpy()), i
+        assert np.array_equal(od, host[2].numpy()) and np.array_equal(ot, host[3].numpy()), i
+        assert np.array_equal(o.legal_mask(), host[1].numpy().view(np.uint64)), i
+        got, tok = host[4].numpy().view(mjo.TOKEN_DTYPE).reshape(B, 4), o.observe_tokens()
+        for name in tok.dtype.names:
+            assert np.array_equal(tok[name], got[name]), (i, name)
+    g.close()
+
+
 def test_standings_match_the_records():
     B = 600
     o = mjo.Oracle(B, 5, mjo.RULES_RED, mjo.MODE_EAST)
