@@ -139,14 +139,16 @@ def test_observation_group_sizes(B):
     g.close()
 
 
-@pytest.mark.parametrize("flags,lpw,seed", [(mjo.RULES_NORED, 32, 3), (mjo.RULES_RED, 64, 4),
+@pytest.mark.parametrize("flags,lpw,seed", [(mjo.RULES_NORED, 32, 3), (mjo.RULES_RED, 0, 4),
                                             (mjo.RULES_RED | mjo.F_ENDGAME | mjo.F_KANDORA_LATE | mjo.F_NAGASHI | mjo.F_ANKAN_ROB | mjo.F_PAO, 32, 5)])
 def test_fused_rollout_large(flags, lpw, seed, monkeypatch):
     """16,384 games x 1,600 fused steps (more than a full hanchan each, so the rare paths are walked many times: wins of every
     kind, kans, robbed kans, abortive draws, busts, game ends), every field and the observation against the
-    oracle, which runs as sixteen shards on the host cores"""
+    oracle, which runs as sixteen shards on the host cores; 32 games per wavefront as on a full machine, or the 8 that the
+    batch size gives (0)"""
     from tests.engines import oracle_rollout_sharded
-    monkeypatch.setenv("MJ_LPW", str(lpw))
+    if lpw:
+        monkeypatch.setenv("MJ_LPW", str(lpw))
     B, steps = 16384, 1600
     g = GpuEngine(B, seed=seed, flags=flags, mode=mjo.MODE_HALF)
     g.step_random(steps)
@@ -156,10 +158,10 @@ def test_fused_rollout_large(flags, lpw, seed, monkeypatch):
     assert np.array_equal(oo, g.observe())
 
 
-@pytest.mark.parametrize("lpw", [16, 32, 64])
+@pytest.mark.parametrize("lpw", [2, 7, 16, 24, 32, 64])
 def test_every_lanes_per_wave_variant(lpw, monkeypatch):
-    """the step kernels exist in three variants (16 / 32 / 64 environments per wavefront); the library picks one
-    by batch size, MJ_LPW forces it"""
+    """the step kernels carry 1 to 32 games per wavefront; the library picks the number by batch size, MJ_LPW forces it (more
+    than 32 count as 32)"""
     monkeypatch.setenv("MJ_LPW", str(lpw))
     B = 777
     o = mjo.Oracle(B, 21, mjo.RULES_RED, mjo.MODE_HALF)
