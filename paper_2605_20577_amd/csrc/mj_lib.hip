@@ -1156,6 +1156,12 @@ ScratchLayout scratch_layout()
   return s;
 }
 size_t scratch_bytes_impl() { return scratch_layout().total; }
+// what the kernels assume of the probe tables that they copy to LDS in a fixed number of 16-byte chunks per lane
+static_assert(kEvalChunks * kAuxBlock >= kTableChunks * kBlock, "the evaluator's blocks copy at least what the step kernels' copy");
+bool tables_fit(const ScratchLayout &sl)
+{
+  return tables().rowid.size() == (size_t)kRowIdBytes && !(sl.probe_bytes & 15) && sl.probe_bytes <= (size_t)kTableChunks * kBlock * 16;
+}
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kAuxBlock - 1) / kAuxBlock); }
 inline unsigned step_blocks(int64_t n, int lanes) { int e = envs_per_block(lanes); return (unsigned)((n + e - 1) / e); }
 // Environments per wavefront for a batch: as few as fill every wavefront slot once (8 per compute unit: two per SIMD is
@@ -1244,7 +1250,7 @@ int static_tables(const StaticTables **out)
     const mjt::SuitTables &t = tables();
     const ScratchLayout sl = scratch_layout();
     const size_t need = sl.nb;                            // everything before the neighbour and shanten tables
-    if (need > kStaticScratchBytes || (sl.probe_bytes & 15)) return MJ_E_UNSUPPORTED;
+    if (need > kStaticScratchBytes || !tables_fit(sl)) return MJ_E_UNSUPPORTED;
     if (hipDeviceGetAttribute(&st.n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || st.n_cu <= 0) return MJ_E_HIP;
     uint8_t *ptr = nullptr;
     if (hipGetSymbolAddress((void **)&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return MJ_E_HIP;
@@ -1307,10 +1313,7 @@ int mj_init(MjHandle **out, void *d_state, void *d_scratch, int64_t B, uint64_t 
   h->ev_valid = false; h->ev_steps = 0;
   const mjt::SuitTables &t = tables();
   const ScratchLayout sl = scratch_layout();
-  if (t.rowid.size() != (size_t)kRowIdBytes || (sl.probe_bytes & 15) || sl.probe_bytes > (size_t)kTableChunks * kBlock * 16) {
-    delete h;
-    return MJ_E_UNSUPPORTED;
-  }
+  if (!tables_fit(sl)) { delete h; return MJ_E_UNSUPPORTED; }
   int dev = 0, lds_max = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
