@@ -2,7 +2,7 @@
 """Benchmark of the batched Riichi Mahjong environment step on one MI355X.
 
 Workload: B = 65,536 four-player games, no-red rules, full hanchan, uniform-random
-legal policy (Philox keyed by seed, env, step, seat), auto-reset; an untimed pre-roll of 2,048 steps that brings the
+legal policy (Philox keyed by seed, env, step, seat), auto-reset; an untimed pre-roll of 4,096 steps that brings the
 batch into its steady state, W warm-up steps, then exactly K timed steps (defaults: 500 and 10,000).
 One "step" = one batched step of all B games = B env steps.  State lives in HBM before the timed region.
 

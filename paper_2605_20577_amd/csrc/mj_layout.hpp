@@ -1,8 +1,8 @@
 // Structure-of-arrays layout of the environment state in HBM.
 //
 // For B environments every field is an array over b, so the lanes of a
-// wavefront (16, 32 or 64 consecutive environments, see mj_lib.hip) touch
-// consecutive addresses.
+// wavefront (1 to 32 consecutive environments in the step kernels, 64 in most
+// others, see mj_lib.hip) touch consecutive addresses.
 // Sections, in this order, each array of length B:
 //   u64 hot : discarded_kinds[4] waits[4] mask[8] meld[4] tenpai_discards   (21 arrays)
 //   u64 cold: yaku[4] result[4] next_waits[4]                               (12 arrays)
@@ -10,8 +10,9 @@
 //   u32 cold: gain[4] glob[7] wall[2][34] (two buffers of 136 tile ids, four per word: the current wall and
 //             the next one) next_serial next_hand[16] next_red (the next deal, made ahead)     (97 arrays)
 //   u8  cold: river[128] (arrays over b like the rest); then history[B][128] u16 (action | seat << 8): the history
-//             is one ROW of 256 bytes PER ENVIRONMENT, not arrays over b, so that the token observation reads a quarter
-//             of it with sixteen word loads (rivers as rows were tried as well: the plane observation kernel lost 17 %)
+//             is one ROW of 256 bytes PER ENVIRONMENT, not arrays over b, so that the token observation and the export
+//             read it as one run, 16 and 4 bytes per lane (rivers as rows were tried as well: the plane observation
+//             kernel lost 17 %)
 // = 1,156 bytes per environment, 288 of them hot.  The "next" arrays are not part of the logical state: they are
 // a pure function of (seed, env id, kyoku_serial + 1), valid when next_serial says so; tenpai_discards is a cache
 // (a function of the hand of the seat to move, valid when its top bit is set).  The step kernels copy the

@@ -694,7 +694,7 @@ __global__ void __launch_bounds__(kAuxBlock) k_standings(void *state, int64_t B,
 
 // Canonical records (AoS, 1,000 bytes) to and from the state (SoA).  Bound by memory; a lane that writes or reads a whole
 // record of its own touches 64 lines per instruction and keeps the record in scratch memory (65,536 games out, in, masks
-// and standings: 184 us, as here 64 us).  Here a block of eight wavefronts takes 64 games: every wavefront reads or writes
+// and standings: 184 us, as here 63 us).  Here a block of eight wavefronts takes 64 games: every wavefront reads or writes
 // one part of the record for 64 games (whole rows of the state, lane = game), the records are put together in LDS, and LDS
 // and the record buffer exchange one contiguous run of 8-byte words.
 constexpr int kRecEnvs = 64, kRecBlock = 64 * kRecParts;                 // LDS stride of a record: 250 words (two-way bank conflicts)
@@ -1181,8 +1181,10 @@ inline int pick_lanes(int64_t B, int n_cu)
 }
 // Hands per wavefront of the evaluator for a batch: as few as fill twelve wavefront slots per compute unit, at most 64.
 // A wavefront's chain grows with the ways and decompositions of its hands, so small batches are spread (us per call, 64
-// hands per wavefront as against this rule: 1,000 hands 14.3 -> 12.9, 4,000 14.9 -> 12.5 to 14.7, 16,000 15.6 -> 13.1,
-// 65,536 17.7 -> 15.4; 8 and 16 slots do as well within 2 us, one hand per wavefront at any size costs 27 us at 16,000).
+// hands per wavefront and the kernel before as against this rule, half of the hands complete: 256 hands 15.4 -> 12.3, 1,000
+// 15.9 -> 12.3, 4,000 17.2 -> 10.0, 16,000 15.9 -> 14.1, 65,536 15.5 -> 15.2; a batch whose slowest hand is the whole
+// chain gains nothing, 13.2 us either way.  8 and 16 slots do as well within 2 us, one hand per wavefront at any size
+// costs 27 us at 16,000).
 inline int eval_lanes(int64_t n, int n_cu)
 {
   const int64_t slots = (int64_t)n_cu * 12, lanes = (n + slots - 1) / slots;
@@ -1390,7 +1392,8 @@ int mj_observe(const MjHandle *h, uint8_t *d_obs, void *stream)
   hipStream_t st = (hipStream_t)stream;
   // Groups of 4 (or 8) games as long as every resident block has one of them, else groups of 32, whose longer runs of
   // stores a full machine needs: a group is a chain of dependent steps, and 32 games of it leave most compute units idle.
-  // us with groups of 4 / 8 / 32: 100 games 14.2 / 20.6 / 23.6, 1,000: 14.1 / 20.3 / 24.7, 3,001: 17.2 / 22.7 / 27.0,
+  // us with groups of 4 / 8 / 32, all with three blocks per compute unit, so that groups of 4 take a second round and the
+  // counter from 3,073 games on and groups of 8 from 6,145 on: 100 games 14.2 / 20.6 / 23.6, 1,000: 14.1 / 20.3 / 24.7, 3,001: 17.2 / 22.7 / 27.0,
   // 4,000: 30.0 / 22.3 / 26.0, 6,000: 40.1 / 23.9 / 25.8, 8,000: 48.9 / 43.3 / 28.1.
   const int64_t blocks = kObsResident * h->n_cu;
   if (h->B <= 4 * blocks) launch_observe<4>(h, d_obs, st);
@@ -1434,8 +1437,8 @@ int mj_reset_done(MjHandle *h, void *stream)
 int mj_sample_random(const MjHandle *h, int8_t *d_actions, void *stream)
 {
   if (!h || !d_actions || ((uintptr_t)d_actions & 3)) return MJ_E_ARG;
-  // a lane per game and seat while that fills the machine at most twice (us, lane per game as against this: 1,000 games
-  // 3.2 / 2.3, 65,536: 3.2 / 2.8, 262,144: 5.0 / 5.2, 2^20: 15.2 / 17.5)
+  // a lane per game and seat while those lanes fill the machine at most once, 2,048 per compute unit (us, lane per game
+  // as against this: 1,000 games 3.2 / 2.3, 65,536: 3.2 / 2.8, 262,144: 5.0 / 5.2, 2^20: 15.2 / 17.5)
   if (h->B <= (int64_t)h->n_cu * 512)
     k_sample_seats<<<(unsigned)((h->B + kSampleEnvs - 1) / kSampleEnvs), kAuxBlock, 0, (hipStream_t)stream>>>(h->d_state, h->B, h->R, h->step, d_actions);
   else
