@@ -862,8 +862,9 @@ MJ_HD void run_ways(const Decomp &d, int w, bool &closed, bool &open_end)
 // EVAL_STEP: a step, where a lane or two evaluate and straight code is the shorter chain (65,536 games: 8.44 us per step,
 //   8.53 with the loop).  One copy per kind of way: where a SIMD has one wavefront nothing hides the fetching of code (1,000
 //   games 5.7 us per step, 6.3 with a copy at every place).
-// EVAL_FULL: a step of a full machine whose wavefronts take turns.  A copy at every place keeps the least alive around each:
-//   65,536 games 0.6 % less time per step than EVAL_STEP (without turns 0.5 % more: 200,000 games and beyond).
+// EVAL_FULL: a step of a full machine.  A copy at every place keeps the least alive around each: 65,536 games 0.6 % less
+//   time per step than EVAL_STEP, 2^20 games 0.9 %.  (Chosen by template: with both forms behind a test of a constant the
+//   compiler lays the kernel out differently and the gain is gone.)
 enum EvalForm { EVAL_STEP, EVAL_FULL, EVAL_BATCH };
 template <EvalForm FORM>
 MJ_HD void eval_decomp(EvalCtx &c, const Decomp &d)

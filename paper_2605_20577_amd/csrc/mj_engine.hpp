@@ -37,7 +37,6 @@ struct Ctx {
   bool need_turn;      // the seat to move still needs its legal mask (step_finish)
   uint32_t live_word;  // the wall word that holds the next live tile, loaded at the start of the step ...
   int live_ptr;        // ... for this draw pointer (-1: nothing loaded)
-  bool full = false;   // a kernel's constant: hands are evaluated as EVAL_FULL
 };
 
 // ------------------------------------------------------------- field access
@@ -109,6 +108,7 @@ MJ_HD void clear_first_and_ippatsu(Ctx &c)
 }
 
 // value of seat s winning on kind w now
+template <EvalForm FORM>
 MJ_HD void eval_seat(Ctx &c, int s, int w, bool tsumo, bool chankan, HandOut &out)
 {
   HandIn q;
@@ -141,7 +141,7 @@ MJ_HD void eval_seat(Ctx &c, int s, int w, bool tsumo, bool chankan, HandOut &ou
   q.n_aka = aka;
   q.kuitan = (c.R.flags & F_KUITAN) ? 1 : 0;
   MJ_RB(ev, true);
-  if (c.full) eval_hand<EVAL_FULL>(&c.L, q, out); else eval_hand<EVAL_STEP>(&c.L, q, out);
+  eval_hand<FORM>(&c.L, q, out);
   MJ_RE(ev, PR_EVAL);
 }
 
@@ -196,6 +196,7 @@ MJ_HD void discard_bits(const uint32_t h[4], uint32_t sw, uint64_t allowed, Mask
 }
 
 // legal actions of the seat to move; the seat's words are read once and handed to the helpers
+template <EvalForm FORM>
 MJ_HD void turn_mask(Ctx &c)
 {
   MJ_STAT(n_turn);
@@ -239,7 +240,7 @@ MJ_HD void turn_mask(Ctx &c)
     else {
       MJ_STAT(n_tsumo_eval);
       HandOut r;
-      eval_seat(c, s, drawn_k, true, false, r);
+      eval_seat<FORM>(c, s, drawn_k, true, false, r);
       if (r.yaku_ok) set_action(m, A_TSUMO);
     }
   }
@@ -365,9 +366,10 @@ MJ_HD void deal_first_draw(Ctx &c)
   c.need_deal = false;
   c.need_turn = true;
 }
+template <EvalForm FORM = EVAL_STEP>
 MJ_HD void step_finish(Ctx &c)
 {
-  if (c.need_turn) turn_mask(c);
+  if (c.need_turn) turn_mask<FORM>(c);
   c.need_turn = false;
 }
 // whole deal from the environment's own wall in HBM
@@ -467,6 +469,7 @@ MJ_HD int pao_seat(Ctx &c, int s, uint64_t yaku)
   return (s + (int)(last >> 9 & 3)) & 3;
 }
 
+template <EvalForm FORM>
 MJ_HD void win(Ctx &c, int winners, bool tsumo, int loser, int w, bool chankan)
 {
   int dealer = dealer_of(c);
@@ -482,7 +485,7 @@ MJ_HD void win(Ctx &c, int winners, bool tsumo, int loser, int w, bool chankan)
   for (int s = 0; s < 4; s++) {
     if (!(winners >> s & 1)) continue;
     HandOut r;
-    eval_seat(c, s, w, tsumo, chankan, r);
+    eval_seat<FORM>(c, s, w, tsumo, chankan, r);
     c.e.yaku[(int64_t)s * c.e.n] = r.yaku;
     c.e.resw[(int64_t)s * c.e.n] = (uint64_t)(uint8_t)r.han | (uint64_t)(uint8_t)r.fu << 8 | (uint64_t)r.units << 16 |
                                    (uint64_t)r.n_dora << 24 | (uint64_t)r.n_ura << 32 | (uint64_t)r.n_aka << 40;
@@ -637,6 +640,7 @@ MJ_HD int settle_discard(Ctx &c)
 
 // can seat o win on kind k discarded (or added to a kan) by someone else?  A fitting tile that can not be
 // won on leaves the seat furiten.
+template <EvalForm FORM>
 MJ_HD bool ron_option(Ctx &c, int o, int k, bool chankan)
 {
   if (!(WAITS(c, o) >> k & 1)) return false;
@@ -646,7 +650,7 @@ MJ_HD bool ron_option(Ctx &c, int o, int k, bool chankan)
     else {
       MJ_STAT(n_ron_eval);
       HandOut r;
-      eval_seat(c, o, k, false, chankan, r);
+      eval_seat<FORM>(c, o, k, false, chankan, r);
       ok = r.yaku_ok;
     }
   }
@@ -885,7 +889,7 @@ MJ_HD void hist_push(Ctx &c, int s, int a)
 // `acts` packs the four seats' actions as signed bytes (seat s in byte s).
 // `sampled_ron` >= 0 says that the actions were drawn from the masks by the library's own sampler (they are legal by
 // construction, so stage 0 is skipped) and carries the seats whose mask offered a win.
-template <int STAGED = 0>
+template <int STAGED = 0, EvalForm FORM = EVAL_STEP>
 MJ_HD void step_env(Ctx &c, uint32_t acts, int sampled_ron = -1)
 {
   c.need_deal = false;
@@ -1076,7 +1080,7 @@ MJ_HD void step_env(Ctx &c, uint32_t acts, int sampled_ron = -1)
     for (int j = 1; j < 4 && hit; j++) {
       MJ_STAT(n_ron_loop);
       const int o = (from + j) & 3;
-      if ((hit >> o & 1) && ron_option(c, o, k, rob)) ron |= 1u << o;
+      if ((hit >> o & 1) && ron_option<FORM>(c, o, k, rob)) ron |= 1u << o;
     }
     MJ_RE(s3r, PR_S3_RON);
     int any = 0;
@@ -1103,7 +1107,7 @@ MJ_HD void step_env(Ctx &c, uint32_t acts, int sampled_ron = -1)
   MJ_RB(win, win_mask != 0);
   MJ_RB(abo, !win_mask && end_abort);
   MJ_RB(exh, !win_mask && !end_abort && exhaust);
-  if (MJ_RARE(win_mask != 0)) win(c, win_mask, (todo & WIN_TSUMO) != 0, win_loser, win_tile, (todo & WIN_ROB) != 0);
+  if (MJ_RARE(win_mask != 0)) win<FORM>(c, win_mask, (todo & WIN_TSUMO) != 0, win_loser, win_tile, (todo & WIN_ROB) != 0);
   else if (end_abort) abortive_draw(c, end_abort);
   else if (exhaust) exhaustive_draw(c);
   MJ_RE(win, PR_WIN);

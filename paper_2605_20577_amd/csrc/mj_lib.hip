@@ -521,12 +521,13 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t
                                                     int n_steps, int auto_reset, int64_t env_lo, int64_t env_hi)
 {
   extern __shared__ __align__(16) uint8_t lds[];
+  constexpr EvalForm kForm = LANES == kMaxLanes ? EVAL_FULL : EVAL_STEP;
   BlockMem m = carve_block(T, lds, LANES ? LANES : lanes_arg);
   const int64_t b = env_lo + m.b;      // the launch covers environments [env_lo, env_hi)
   const bool active = m.lane_on && b < env_hi;
   Ctx c;
   c.e = block_env(m, state, B, active ? b : 0); c.L = m.L; c.R = R; c.env_id = R.env_id_base + (uint32_t)b;
-  c.need_deal = false; c.need_turn = false; c.live_ptr = -1; c.full = LANES == kMaxLanes && TURNS;
+  c.need_deal = false; c.need_turn = false; c.live_ptr = -1;
   const TableRegs tr = table_fetch(T);
   if (active) { load_hot(m, state, B, b); load_glob(c.e, c.g); }
   table_commit(T, lds, tr);
@@ -564,7 +565,7 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t
       acts = sample_actors(c, step0 + t, ron_offered);
       MJ_RE(sa, PR_SAMPLE);
       MJ_RB(st, true);
-      step_env<1>(c, acts, ron_offered);
+      step_env<1, kForm>(c, acts, ron_offered);
       MJ_RE(st, PR_STEP);
       MJ_RB(rs, auto_reset && c.g.terminated);
       if (auto_reset && c.g.terminated) reset_env(c, false);
@@ -574,7 +575,7 @@ __global__ void __launch_bounds__(kBlock, MJ_OCC) k_rollout(void *state, int64_t
     deal_stage(c, active, state, B, b);
     MJ_RE(dl, PR_DEAL);
     MJ_RB(fin, active && c.need_turn);
-    if (active) step_finish(c);
+    if (active) step_finish<kForm>(c);
     MJ_RE(fin, PR_FINISH);
     MJ_RE(loop, PR_LOOP);
   }

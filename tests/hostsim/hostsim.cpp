@@ -34,7 +34,6 @@ static Ctx ctx_of(Sim *h, int64_t b)
   c.e = make_env(h->state.data(), h->B, b);
   c.L = h->L; c.R = h->R; c.env_id = h->R.env_id_base + (uint32_t)b;
   c.need_deal = false; c.need_turn = false; c.live_ptr = -1;
-  c.full = b & 1;                               // every other game evaluates its hands as on a full machine
   return c;
 }
 static void reset_env(Ctx &c, bool first)
@@ -56,6 +55,12 @@ static uint32_t pack4(const int a[4])
 }
 static void step_and_deal(Ctx &c, const int a[4], int sampled_ron = -1)
 {
+  if (c.env_id & 1) {                           // every other game evaluates its hands as on a full machine
+    step_env<0, EVAL_FULL>(c, pack4(a), sampled_ron);
+    if (c.need_deal) deal(c, true);
+    step_finish<EVAL_FULL>(c);
+    return;
+  }
   step_env(c, pack4(a), sampled_ron);
   if (c.need_deal) deal(c, true);
   step_finish(c);
