@@ -1201,7 +1201,7 @@ inline int check(hipError_t e) { return e == hipSuccess ? MJ_OK : MJ_E_HIP; }
 // Whether a fused launch over n environments at 32 per wavefront lets the wavefronts of a SIMD take turns.  A launch that is
 // resident at once ends with its slowest wavefront, and turns make the two alike.  In a longer one a finished block is
 // replaced, and uneven wavefronts only start the next blocks earlier; alike they end together, round by round, which pays
-// again when a last round of about half a machine then has its SIMDs to itself.  After `rounds` full rounds it does from a
+// again when a last round of blocks of about half a machine then has its SIMDs to itself.  After `rounds` full rounds it does from a
 // last round of rounds / (2 rounds + 2) of the machine on, up to 7/8.  512 steps with turns over the same without, x =
 // machines full of games: x = 1.1: 1.04, 1.24: 1.08, 1.28: 0.96, 1.5: 0.96, 2.3: 1.02, 2.36: 0.97, 3.3: 1.02, 3.5: 0.97, 6.3:
 // 1.02, 6.6: 0.98, 8: 1.03, 16: 1.02.  20 steps gain and lose half as much.
